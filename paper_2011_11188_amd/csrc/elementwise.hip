@@ -312,59 +312,138 @@ static bool pool_vec_ok(int64_t n, int64_t h, int64_t w, int64_t c, mdnn_dtype_t
 }
 
 // ---------------------------------------------------------------------------
-// losses: one block; waves own rows in a fixed order, block sum in a fixed order
+// losses: rows in a fixed order, sums in a fixed order
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
 constexpr int LOSS_THREADS = 1024;
 
+// Cross-entropy, G lanes per row (V values per lane, kept in registers, so a
+// row is read once): row r's lane l holds columns l, l + G, ...  Each block
+// takes `rows` consecutive rows, its row groups in turn; the row losses are
+// added in a fixed order.  HBM-bound (4 + es bytes per logit): one block
+// walking all rows (the loss sum has no scratch memory to be spread over)
+// took 3752 us for 4096 x 1000 fp16 gradients, 24.6 MB; spread over the chip
+// it takes 15.4 us, the second launch included.
+//
+// With more than one block a block leaves its loss sum, and the lse of its
+// first row, in that row's first stored gradients (8 bytes), and
+// softmax_xent_finish_kernel adds the sums and writes the gradients those
+// bytes displaced: the same expression of the same values, so the same bits.
 template <class OutT>
+__device__ __forceinline__ typename OutT::storage xent_grad(float z, float lse, bool hit, bool ok, float S,
+                                                            float inv_b) {
+  float g = S * (expf(z - lse) - (hit ? 1.0f : 0.0f)) * inv_b;
+  if (!ok) g = NAN;
+  return from_f<OutT>(g);
+}
+
+// the 8 bytes of a row's first gradients as two floats
+template <class OutT> constexpr int xent_stash() { return 8 / (int)sizeof(typename OutT::storage); }
+template <class S>
+__device__ __forceinline__ void stash_put(S* d, float a, float b) {
+  if constexpr (sizeof(S) == 4) {
+    d[0] = a, d[1] = b;
+  } else {
+    const uint32_t ua = __builtin_bit_cast(uint32_t, a), ub = __builtin_bit_cast(uint32_t, b);
+    d[0] = (uint16_t)ua, d[1] = (uint16_t)(ua >> 16), d[2] = (uint16_t)ub, d[3] = (uint16_t)(ub >> 16);
+  }
+}
+template <class S>
+__device__ __forceinline__ void stash_get(const S* d, float& a, float& b) {
+  if constexpr (sizeof(S) == 4) {
+    a = d[0], b = d[1];
+  } else {
+    a = __builtin_bit_cast(float, (uint32_t)d[0] | ((uint32_t)d[1] << 16));
+    b = __builtin_bit_cast(float, (uint32_t)d[2] | ((uint32_t)d[3] << 16));
+  }
+}
+
+template <class OutT, int G, int V>
 __global__ void __launch_bounds__(LOSS_THREADS)
-softmax_xent_kernel(int64_t B, int64_t C, const float* __restrict__ z, int64_t ldl,
-                    const int32_t* __restrict__ labels, const float* __restrict__ scale_p,
-                    float* __restrict__ loss_out, typename OutT::storage* __restrict__ dz,
-                    int64_t ldd) {
-  __shared__ float wsum[LOSS_THREADS / 64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nw = LOSS_THREADS / 64;
+softmax_xent_kernel(int64_t B, int64_t C, const float* z, int64_t ldl, const int32_t* __restrict__ labels,
+                    const float* __restrict__ scale_p, float* __restrict__ loss_out, typename OutT::storage* dz,
+                    int64_t ldd, int64_t rows) {
+  __shared__ float gsum[LOSS_THREADS / G];
+  __shared__ float lse0;
+  const int l = threadIdx.x % G, grp = threadIdx.x / G, ng = blockDim.x / G;
   const float S = scale_p ? *scale_p : 1.0f;
   const float inv_b = 1.0f / (float)B;
-  float acc = 0.0f;  // lane 0: this wave's rows, in order
-  for (int64_t r = wave; r < B; r += nw) {
+  const int64_t r0 = (int64_t)blockIdx.x * rows, r1 = r0 + rows < B ? r0 + rows : B;
+  const bool alone = gridDim.x == 1;
+  float acc = 0.0f;  // this group's rows, in order
+  for (int64_t r = r0 + grp; r < r1; r += ng) {
     const float* zr = z + r * ldl;
-    float m = -INFINITY;
-    for (int64_t j = lane; j < C; j += 64) m = fmaxf(m, zr[j]);
-    m = wave_max(m);
-    float se = 0.0f;
-    for (int64_t j = lane; j < C; j += 64) se += expf(zr[j] - m);
-    se = wave_sum(se);
-    const float lse = m + logf(se);
     const int32_t lab = labels[r];
     const bool ok = lab >= 0 && lab < C;
-    for (int64_t j = lane; j < C; j += 64) {
-      const float p = expf(zr[j] - lse);
-      float g = S * (p - (j == lab ? 1.0f : 0.0f)) * inv_b;
-      if (!ok) g = NAN;
-      dz[r * ldd + j] = from_f<OutT>(g);
+    float v[V];
+    float m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = l + i * G < C ? zr[l + i * G] : -INFINITY;
+    const float zl = zr[ok ? lab : 0];
+#pragma unroll
+    for (int i = 0; i < V; ++i) m = fmaxf(m, v[i]);
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    float se = 0.0f;
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (l + i * G < C) se += expf(v[i] - m);
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) se += __shfl_xor(se, o, 64);
+    const float lse = m + logf(se);
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const int j = l + i * G;
+      // (the block's first row leaves its first columns to the stash)
+      if (j < C && (alone || r != r0 || j >= xent_stash<OutT>()))
+        dz[r * ldd + j] = xent_grad<OutT>(v[i], lse, j == lab, ok, S, inv_b);
     }
-    if (lane == 0) acc += ok ? (lse - zr[lab]) : NAN;
+    acc += ok ? (lse - zl) : NAN;
+    if (r == r0 && l == 0) lse0 = lse;
   }
-  if (lane == 0) wsum[wave] = acc;
+  if (l == 0) gsum[grp] = acc;
   __syncthreads();
   if (threadIdx.x == 0) {
     float t = 0.0f;
-    for (int k = 0; k < nw; ++k) t += wsum[k];
-    *loss_out = t * inv_b;
+    for (int k = 0; k < ng; ++k) t += gsum[k];
+    if (alone)
+      *loss_out = t * inv_b;
+    else
+      stash_put(dz + r0 * ldd, t, lse0);
   }
+}
+
+// One block: thread t adds the loss sums of blocks t, t + 1024, ... in order
+// (then a fixed tree over the threads) and restores those rows' first gradients.
+template <class OutT>
+__global__ void __launch_bounds__(LOSS_THREADS)
+softmax_xent_finish_kernel(int64_t B, int64_t nblocks, int64_t rows, const float* __restrict__ z, int64_t ldl,
+                           const int32_t* __restrict__ labels, int64_t C, const float* __restrict__ scale_p,
+                           float* __restrict__ loss_out, typename OutT::storage* __restrict__ dz, int64_t ldd) {
+  __shared__ float red[LOSS_THREADS];
+  constexpr int K = xent_stash<OutT>();
+  const float S = scale_p ? *scale_p : 1.0f;
+  const float inv_b = 1.0f / (float)B;
+  float acc = 0.0f;
+  for (int64_t b = threadIdx.x; b < nblocks; b += LOSS_THREADS) {
+    const int64_t r = b * rows;
+    float sum, lse;
+    stash_get(dz + r * ldd, sum, lse);
+    const int32_t lab = labels[r];
+    const bool ok = lab >= 0 && lab < C;
+    float v[K];
+#pragma unroll
+    for (int j = 0; j < K; ++j) v[j] = z[r * ldl + j];
+#pragma unroll
+    for (int j = 0; j < K; ++j) dz[r * ldd + j] = xent_grad<OutT>(v[j], lse, j == lab, ok, S, inv_b);
+    acc += sum;
+  }
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  for (int s = LOSS_THREADS / 2; s > 0; s >>= 1) {
+    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *loss_out = red[0] * inv_b;
 }
 
 // Few classes (C <= 32): one thread per row, so all rows run at once (a
@@ -925,6 +1004,43 @@ mdnn_status_t launch_xent_rows(int64_t B, int64_t C, const float* logits, int64_
 }
 }  // namespace
 
+// Rows spread over the chip: four row groups per block, at most 4096 blocks
+// (the finish kernel then reads at most four stashes per thread).  One block
+// does it all, in one launch, for up to 32 rows (two rows per wave: less than
+// the second launch costs), and where the gradients overlap the logits (the
+// finish kernel reads logits again).
+template <class OutT>
+static mdnn_status_t launch_xent(int64_t B, int64_t C, const float* z, int64_t ldl, const int32_t* labels,
+                                 const float* scale, float* loss_out, void* dlogits, int64_t ldd, hipStream_t st) {
+  typedef typename OutT::storage S;
+  S* dz = (S*)dlogits;
+  const uintptr_t z0 = (uintptr_t)z, z1 = (uintptr_t)(z + (B - 1) * ldl + C);
+  const uintptr_t d0 = (uintptr_t)dz, d1 = (uintptr_t)(dz + (B - 1) * ldd + C);
+  const bool one = B <= 32 || (z0 < d1 && d0 < z1);
+  const bool few = C <= SMALL_C;
+  const int per = few ? 32 : 4;  // rows a block of 256 threads has in flight
+  int64_t nblocks = 1, rows = B;
+  if (!one) {
+    rows = ceil_div(ceil_div(B, per), 4096) * per;
+    nblocks = ceil_div(B, rows);
+  }
+  const dim3 grid((unsigned)nblocks), blk(one ? LOSS_THREADS : 256);
+  if (few)
+    hipLaunchKernelGGL((softmax_xent_kernel<OutT, 8, 4>), grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out, dz,
+                       ldd, rows);
+  else if (C <= 256)
+    hipLaunchKernelGGL((softmax_xent_kernel<OutT, 64, 4>), grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out, dz,
+                       ldd, rows);
+  else
+    hipLaunchKernelGGL((softmax_xent_kernel<OutT, 64, 16>), grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out,
+                       dz, ldd, rows);
+  MDNN_TRY(check_launch("softmax_xent_kernel"));
+  if (nblocks == 1) return MDNN_SUCCESS;
+  hipLaunchKernelGGL((softmax_xent_finish_kernel<OutT>), dim3(1), dim3(LOSS_THREADS), 0, st, B, nblocks, rows, z, ldl,
+                     labels, C, scale, loss_out, dz, ldd);
+  return check_launch("softmax_xent_finish_kernel");
+}
+
 bool softmax_xent_db_ok(int64_t B, int64_t C) {
   return B >= 1 && B <= LOSS_THREADS && C >= 1 && C <= SMALL_C && (size_t)B * C * sizeof(float) <= XENT_DB_LDS;
 }
@@ -950,16 +1066,15 @@ extern "C" mdnn_status_t mdnn_softmax_xent(int64_t B, int64_t C, const float* lo
     return fail(MDNN_ERR_MISALIGNED, "softmax_xent: misaligned buffer");
   clear_error();
   hipStream_t st = as_stream(stream);
-  if (C <= SMALL_C) return launch_xent_rows(B, C, logits, ldl, labels, loss_scale, loss_out, dlogits, ldd,
-                                            dlogits_type, nullptr, nullptr, st);
+  if (C <= SMALL_C && (B <= LOSS_THREADS || C < 4))
+    return launch_xent_rows(B, C, logits, ldl, labels, loss_scale, loss_out, dlogits, ldd, dlogits_type, nullptr,
+                            nullptr, st);
   switch (dlogits_type) {
-    case MDNN_F32: hipLaunchKernelGGL(softmax_xent_kernel<F32>, dim3(1), dim3(LOSS_THREADS), 0, st, B, C, logits, ldl, labels, loss_scale, loss_out, (float*)dlogits, ldd); break;
-    case MDNN_F16: hipLaunchKernelGGL(softmax_xent_kernel<F16>, dim3(1), dim3(LOSS_THREADS), 0, st, B, C, logits, ldl, labels, loss_scale, loss_out, (uint16_t*)dlogits, ldd); break;
-    default: hipLaunchKernelGGL(softmax_xent_kernel<BF16>, dim3(1), dim3(LOSS_THREADS), 0, st, B, C, logits, ldl, labels, loss_scale, loss_out, (uint16_t*)dlogits, ldd); break;
+    case MDNN_F32: return launch_xent<F32>(B, C, logits, ldl, labels, loss_scale, loss_out, dlogits, ldd, st);
+    case MDNN_F16: return launch_xent<F16>(B, C, logits, ldl, labels, loss_scale, loss_out, dlogits, ldd, st);
+    default: return launch_xent<BF16>(B, C, logits, ldl, labels, loss_scale, loss_out, dlogits, ldd, st);
   }
-  return check_launch("softmax_xent_kernel");
 }
-
 extern "C" mdnn_status_t mdnn_mse_loss(int64_t B, int64_t O, const float* y, const float* t,
                                        const float* loss_scale, float* loss_out, void* dy,
                                        mdnn_dtype_t dy_type, mdnn_stream_t stream) {

@@ -185,6 +185,42 @@ def test_softmax_xent(mdnn, dt, shape):
     assert norm_max_err(host64(dz), dzw) <= (1e-6 if dt == "f32" else 2.0 ** -8)
 
 
+# Rows over several blocks (more than 32, or more than 1024 rows of at most 32
+# classes): one row past a block, 4 classes (16-bit: the whole row is the
+# block's stash), either side of 32 and 256 classes, several rows per group
+# (more than 16384 rows), a row stride that leaves rows 2-byte aligned.
+@pytest.mark.parametrize("shape", [(33, 33), (1025, 4), (1057, 32), (130, 256), (131, 257), (64, 1024), (16390, 40)])
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+def test_softmax_xent_rows_over_blocks(mdnn, dt, shape):
+    import torch
+    B, Cn = shape
+    ldl, ldd = Cn + 3, Cn + 1
+    z = W.normal((B, ldl), 27, 1, "f32", 3.0)
+    lab = W.rng(27, 2).integers(0, Cn, B).astype(np.int32)
+    loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+    dz = empty((B, ldd), dt)
+    Z, L = dev(z, "f32"), dev(lab, "i32")
+    scale = torch.tensor([256.0], dtype=torch.float32, device="cuda")
+    mdnn.mdnn_softmax_xent(B, Cn, Z, ldl, L, scale, loss, dz, ldd, DT[dt])
+    torch.cuda.synchronize()
+    lw, dzw = ops.softmax_xent(z[:, :Cn].astype(np.float64), lab, 256.0)
+    assert abs(loss.item() - lw) <= 1e-5 * abs(lw)
+    assert norm_max_err(host64(dz)[:, :Cn], dzw) <= (1e-6 if dt == "f32" else 2.0 ** -8)
+    # a bad label in the last block's first row: that row and the loss are NaN, its neighbours unchanged
+    keep = host64(dz)[:, :Cn].copy()
+    bad = (B - 1) // 32 * 32
+    L[bad] = -1
+    mdnn.mdnn_softmax_xent(B, Cn, Z, ldl, L, scale, loss, dz, ldd, DT[dt])
+    got = host64(dz)[:, :Cn]
+    assert math.isnan(loss.item()) and np.isnan(got[bad]).all()
+    assert np.array_equal(np.delete(got, bad, 0), np.delete(keep, bad, 0))
+    if dt == "f32":   # gradients written over the logits: the single-block launch, the same gradients
+        Zi = Z.clone()
+        mdnn.mdnn_softmax_xent(B, Cn, Zi, ldl, L, scale, loss, Zi, ldl, DT[dt])
+        gi = host64(Zi)[:, :Cn]
+        assert np.array_equal(np.delete(gi, bad, 0), np.delete(keep, bad, 0))
+
+
 def test_softmax_uniform_logits_ln10_and_bad_labels(mdnn):
     import torch
     B = 64
