@@ -687,6 +687,16 @@ static mdnn_status_t gemm_dispatch16(mdnn_layout_t layout, int64_t M, int64_t N,
       case MDNN_NT: MDNN_TRY((run_gemm_lds<T, OutT, true, true>(la, lb, M, N, K, ep, splits, st))); break;
       default: MDNN_TRY((run_gemm_lds<T, OutT, false, false>(la, lb, M, N, K, ep, splits, st)));
     }
+  } else if (!(va && vb && choose_tile(M, N, splits) == TILE_256x256) &&
+             !(gemm_tile_override() >= TILE_256x256 && gemm_tile_override() <= TILE_64x64) &&
+             gemm_reg_ok(T::id, layout, M, N, K, lda, ldb, splits)) {
+    // What the pipelined kernel refuses (odd leading dimensions, K or extents,
+    // few tiles).  Against the general kernel below: bf16 NN 1000 x 777 x 1531
+    // 117 -> 17 us, TN 4001 x 3999 x 4003 732 -> 196 us, NN 1000^3 22 -> 12 us,
+    // NN 64 x 64 x 4096 69 -> 21 us.  Where rows are 16-byte aligned and there
+    // is a 256 x 256 tile per CU the general kernel's larger tile is still
+    // better (fp16 NT 7488 x 4032 x 104: 36.6 against 39.0 us).
+    MDNN_TRY(gemm_reg(T::id, OutT::id, layout, M, N, K, A, lda, B, ldb, ep, splits, st));
   } else {
     switch (layout) {
       case MDNN_NN:
@@ -719,6 +729,13 @@ static mdnn_status_t gemm_dispatch32(mdnn_layout_t layout, int64_t M, int64_t N,
     ep.partial = (float*)ws;
     ep.k_per_split = plan.k_per_split;
     splits = plan.splits;
+  }
+  // fp32 on the matrix cores (157 TFLOP/s; the vector-ALU kernel below stays
+  // under 79): NN 1024 x 2048 x 2048 198 -> 87 us, 4096^3 2045 -> 1008 us,
+  // 1000^3 89 -> 29 us.  Contiguous extents below 4 keep the kernel below.
+  if (gemm_reg_ok(MDNN_F32, layout, M, N, K, lda, ldb, splits)) {
+    MDNN_TRY(gemm_reg(MDNN_F32, MDNN_F32, layout, M, N, K, A, lda, B, ldb, ep, splits, st));
+    return split ? reduce_epilogue<F32, F32>(ws, splits, M, N, ep_in, st) : MDNN_SUCCESS;
   }
   switch (layout) {
     case MDNN_NN:

@@ -170,6 +170,16 @@ inline mdnn_status_t run_gemm16(const SrcA& a, const SrcB& b, int64_t M, int64_t
   return check_launch("gemm_mfma_kernel");
 }
 
+// The register-staged kernel (gemm_reg.hip): any element alignment and
+// leading dimension, 16-bit or fp32 operands.  ok: chunks of 16 bytes along
+// each operand's contiguous dimension exist (that extent >= 8 16-bit or 4
+// fp32 elements) and 32-bit byte offsets reach it.
+bool gemm_reg_ok(mdnn_dtype_t ab, mdnn_layout_t layout, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                 int splits);
+mdnn_status_t gemm_reg(mdnn_dtype_t ab, mdnn_dtype_t d, mdnn_layout_t layout, int64_t M, int64_t N, int64_t K,
+                       const void* A, int64_t lda, const void* B, int64_t ldb, const Epilogue& ep, int splits,
+                       hipStream_t st);
+
 // Plain-matrix operand of the pipelined kernel: `kc` = K-contiguous.
 struct LdsOperand {
   const void* p;
@@ -222,7 +232,7 @@ typedef lds::Tile<128, 128, 2, 2, 1> Tile128Deep;
 typedef lds::Tile<64, 64, 2, 2, 4> Tile64;
 
 template <class T, class OutT, bool A_KC, bool B_KC>
-inline mdnn_status_t run_gemm_lds(const LdsOperand& a, const LdsOperand& b, int64_t M, int64_t N,
+mdnn_status_t run_gemm_lds(const LdsOperand& a, const LdsOperand& b, int64_t M, int64_t N,
                                   int64_t K, const Epilogue& ep, int splits, hipStream_t stream) {
   const int o = gemm_tile_override();
   if (o == TILE_AUTO && N <= 64 && M > 64)
@@ -250,6 +260,26 @@ inline mdnn_status_t run_gemm_lds(const LdsOperand& a, const LdsOperand& b, int6
     launch_gemm_lds<T, OutT, lds::Tile128, A_KC, B_KC>(a, b, M, N, K, ep, splits, stream);
   return check_launch("gemm_lds_kernel");
 }
+
+// instantiated in gemm_pipe_f16.hip and gemm_pipe_bf16.hip (they take minutes
+// to compile)
+#define MDNN_RUN_GEMM_LDS(EXT, T)                                                                                   \
+  EXT template mdnn_status_t run_gemm_lds<T, T, true, false>(const LdsOperand&, const LdsOperand&, int64_t, int64_t, \
+                                                            int64_t, const Epilogue&, int, hipStream_t);            \
+  EXT template mdnn_status_t run_gemm_lds<T, T, true, true>(const LdsOperand&, const LdsOperand&, int64_t, int64_t,  \
+                                                           int64_t, const Epilogue&, int, hipStream_t);             \
+  EXT template mdnn_status_t run_gemm_lds<T, T, false, false>(const LdsOperand&, const LdsOperand&, int64_t,         \
+                                                             int64_t, int64_t, const Epilogue&, int, hipStream_t);  \
+  EXT template mdnn_status_t run_gemm_lds<T, F32, true, false>(const LdsOperand&, const LdsOperand&, int64_t,        \
+                                                              int64_t, int64_t, const Epilogue&, int, hipStream_t); \
+  EXT template mdnn_status_t run_gemm_lds<T, F32, true, true>(const LdsOperand&, const LdsOperand&, int64_t,         \
+                                                             int64_t, int64_t, const Epilogue&, int, hipStream_t);  \
+  EXT template mdnn_status_t run_gemm_lds<T, F32, false, false>(const LdsOperand&, const LdsOperand&, int64_t,       \
+                                                               int64_t, int64_t, const Epilogue&, int, hipStream_t);
+#ifndef MDNN_PIPE_UNIT
+MDNN_RUN_GEMM_LDS(extern, F16)
+MDNN_RUN_GEMM_LDS(extern, BF16)
+#endif
 
 // Pipelined kernel with explicit tile and loaders (the convolutions).
 template <class T, class OutT, class TL, int NS, class LA, class LB>

@@ -1,0 +1,687 @@
+// Register-staged GEMM mainloop for gfx950: the products whose operands the
+// direct-to-LDS mainloop (gemm_lds.h) cannot fetch -- rows that start on any
+// element (odd leading dimensions and sizes, any K), and fp32 operands --
+// on the matrix cores (v_mfma_f32_16x16x32_{f16,bf16} and
+// v_mfma_f32_16x16x4_f32), fp32 accumulation.
+//
+// An operand tile is 128 bytes of k per row (64 16-bit or 32 fp32 elements),
+// fetched as 16-byte chunks of E consecutive elements along the operand's
+// contiguous dimension: global memory -> registers (one unaligned 16-byte
+// load per chunk; gfx950 takes any element address) -> LDS (16-byte writes)
+// -> fragments.  NR register sets keep the loads of NR - 1 tiles in flight
+// behind the MFMAs of the current one; LDS holds two tiles, so a K step has
+// one barrier.
+//
+// Every load stays inside the operand: a chunk that would run past the end
+// starts earlier and is shifted into place, and elements outside the valid
+// range (k past the end, zero padding of an image) are cleared, both in
+// registers before the LDS write and only where a step can hold such a chunk
+// (the loaders' `plain` and `fx`).  Chunks past M or N of an operand whose contiguous dimension
+// is M or N are fetched from inside the row: they feed outputs that are
+// never stored.
+//
+// What bounds it: fp32 products the matrix cores (busy 86% of the time at
+// 4096^3, 136 TFLOP/s; 66% at 1024 x 2048 x 2048 where the launch and the
+// first loads show); 16-bit ones the LDS writes and their barrier (4001 x
+// 3999 x 4003: 610-650 TFLOP/s, about half of the direct-to-LDS kernel on
+// aligned operands).  Reading the second half step's fragments ahead of the
+// first half's MFMAs spilled registers and gained nothing.
+//
+// LDS layouts: as in gemm_lds.h for 16-bit elements and for K-contiguous
+// fp32 tiles (128-byte rows, 16-byte chunk c of row r at c ^ ((r >> 1) & 7));
+// an MN-contiguous fp32 tile is stored k-row by k-row, its 64-byte block b at
+// b ^ ((k >> 2) & 3), so that the four k-rows one fragment read touches lie
+// in different banks.  An fp32 fragment is 16 rows x 16 k: lane group g
+// holds k = 4g .. 4g + 3, one MFMA per k mod 4 (both operands alike).
+#pragma once
+
+#include "gemm_lds.h"
+
+namespace mdnn {
+namespace reg {
+
+using lds::LoadPos;
+
+template <class T>
+struct El {
+  static constexpr int ES = (int)sizeof(typename T::storage);
+  static constexpr int E = 16 / ES;    // elements per chunk
+  static constexpr int BK = 128 / ES;  // k per step
+};
+
+// One chunk at any element address.
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+template <int ES>
+__device__ __forceinline__ uint4 load_chunk(const char* p) {
+  typedef std::conditional_t<ES == 2, u32x4_a2, u32x4_a4> V;
+  const V v = *(const __attribute__((address_space(1))) V*)p;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// How a loaded chunk becomes the wanted one: element e of it is loaded
+// element e + d, cleared unless lo <= e < hi.
+__device__ __forceinline__ uint32_t fixup(int d, int lo, int hi) {
+  return (uint32_t)(d + 16) | ((uint32_t)lo << 8) | ((uint32_t)hi << 16);
+}
+template <int ES>
+__device__ __forceinline__ uint4 apply_fix(uint4 v, uint32_t fx) {
+  const int d = (int)(fx & 0xffu) - 16, lo = (int)((fx >> 8) & 0xffu), hi = (int)((fx >> 16) & 0xffu);
+  if (__any(d != 0)) {
+    constexpr int B = 8 * ES;
+    typedef unsigned __int128 u128;
+    u128 x = ((u128)(((uint64_t)v.w << 32) | v.z) << 64) | (((uint64_t)v.y << 32) | v.x);
+    x = d >= 0 ? x >> (B * (d & 15)) : x << (B * (-d & 15));
+    const uint64_t l = (uint64_t)x, h = (uint64_t)(x >> 64);
+    v = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+  }
+  const int bits = lo < hi ? (int)(((1u << hi) - 1u) & ~((1u << lo) - 1u)) : 0;  // valid elements
+  uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if constexpr (ES == 2) {
+      const uint32_t a = (uint32_t)__builtin_amdgcn_sbfe(bits, 2 * j, 1), b = (uint32_t)__builtin_amdgcn_sbfe(bits, 2 * j + 1, 1);
+      w[j] &= __builtin_amdgcn_perm(b, a, 0x05040100u);
+    } else {
+      w[j] &= (uint32_t)__builtin_amdgcn_sbfe(bits, j, 1);
+    }
+  }
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// What load i of this lane fetches (as lds::load_pos, for either element size).
+template <class T, bool KC, int W, int L>
+__device__ __forceinline__ LoadPos load_pos(int wave, int lane, int i) {
+  if constexpr (sizeof(typename T::storage) == 2) {
+    return lds::load_pos<KC, W, L>(wave, lane, i);
+  } else if constexpr (KC) {
+    const int r = (wave * L + i) * 8 + (lane >> 3);
+    return {r, ((lane & 7) ^ ((r >> 1) & 7)) * 4};
+  } else {
+    constexpr int LPR = W / 4;     // lanes per k-row
+    constexpr int KPB = 64 / LPR;  // k-rows per 1 KB
+    const int k = (wave * L + i) * KPB + lane / LPR, pc = lane % LPR;
+    return {k, (((pc >> 2) ^ ((k >> 2) & 3)) << 4) + (pc & 3) * 4};
+  }
+}
+
+// ---------------------------------------------------------------- loaders
+
+struct MatArgs {
+  const void* p;
+  int64_t ld, MN, K;
+};
+
+// Plain matrix, K-contiguous ([MN][ld >= K]) or MN-contiguous ([K][ld >= MN]).
+// K >= E, and MN >= E when MN-contiguous; byte offsets within the operand
+// (K-contiguous) or within one step (MN-contiguous) below 2^32.
+template <class T, bool KC_, int W, int L>
+struct MatLoader {
+  static constexpr bool KC = KC_;
+  static constexpr bool ANY_STEP = false;  // chunks to fix only in the last step
+  static constexpr bool RUNS = false;      // the operand's columns are the product's
+  static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
+  typedef MatArgs Args;
+  const char* base;
+  int64_t step, ld, MN, K, kbeg, kend;
+  int32_t last;  // the step that ends at kend
+  uint32_t off[L];
+  int32_t kpos[L];  // KC: k of the chunk within a step; else its k-row
+
+  __device__ __forceinline__ void init(const MatArgs& a, int64_t mn0, int64_t kb, int64_t ke, int wave, int lane) {
+    ld = a.ld, MN = a.MN, K = a.K, kbeg = kb, kend = ke;
+    last = (int32_t)((ke - kb + BK - 1) / BK) - 1;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const LoadPos q = load_pos<T, KC, W, L>(wave, lane, i);
+      if constexpr (KC) {
+        int64_t row = mn0 + q.r;
+        if (row >= MN) row = MN - 1;
+        kpos[i] = q.c;
+        off[i] = (uint32_t)((row * ld + q.c) * ES);
+      } else {
+        int64_t mn = mn0 + q.c;
+        if (mn >= MN) mn = MN - E;
+        kpos[i] = q.r;
+        off[i] = (uint32_t)(((int64_t)q.r * ld + mn) * ES);
+      }
+    }
+    step = (KC ? (int64_t)BK : BK * ld) * ES;
+    base = (const char*)a.p + (KC ? kbeg : kbeg * ld) * ES;
+  }
+  // CHECK = false: a step before the last
+  template <bool CHECK>
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+    const char* kb = base + (int64_t)t * step;
+    if (!CHECK || t < last) {
+#pragma unroll
+      for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + off[i]);
+      return;
+    }
+    // the last step: chunks past the operand's end are fetched from inside it
+#pragma unroll
+    for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + ((int64_t)off[i] - (int64_t)back(t, i) * ES));
+  }
+  // elements that chunk i of the last step is fetched early by
+  __device__ __forceinline__ int64_t back(int t, int i) {
+    const int64_t k0 = kbeg + (int64_t)t * BK;
+    if constexpr (KC) {
+      const int64_t over = k0 + kpos[i] + E - K;
+      return over > 0 ? over : 0;
+    } else {
+      const int64_t over = (int64_t)(off[i] / ES) - ((K - 1 - k0) * ld + MN - E);
+      return over > 0 ? over : 0;
+    }
+  }
+  __device__ __forceinline__ bool plain(int t) { return t < last; }
+  __device__ __forceinline__ uint32_t fx(int t, int i) {
+    const int64_t left = kend - (kbeg + (int64_t)t * BK + kpos[i]);
+    const int hi = left <= 0 ? 0 : !KC || left > E ? E : (int)left;
+    return fixup(hi ? (int)back(t, i) : 0, 0, hi);
+  }
+};
+
+// Convolutions (NHWC, stride 1): for one filter row the S * C elements under
+// an output pixel are one run of memory in the image row, and one run of the
+// filter.  The reduction is walked run by run, each padded to Lp, a multiple
+// of the chunk, so that a chunk is a piece of one run for any channel count;
+// elements past the run and left or right of the image are cleared.
+
+// x / d for x * (d - 1) < 2^32 (magic: ceil(2^32 / d), 0 for d = 1).
+using lds::fast_div;
+
+struct RunArgs {
+  const void* p;
+  int32_t total;           // elements of p
+  int32_t rows, L, Lp;     // filter rows, elements per run, padded
+  uint32_t magic_lp;
+  int32_t hs, wsC, C;      // image rows, elements per image row, channels
+  int32_t ho, wo;          // output grid
+  int32_t padr, pads;      // rows above, pixels left
+  uint32_t magic_a, magic_b;  // RunColsLoader: of wo, ho; RunFilterT: of the run's channels
+  int64_t M;               // output pixels (RunRowsLoader), filters (RunFilter)
+};
+
+__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
+
+// image chunk: element offset o (may lie outside), x position q of its first
+// element in the image row, e of it in the run
+template <int E>
+__device__ __forceinline__ uint32_t run_fix(bool ok, int o, int total, int q, int wsC, int left) {
+  int lo = q < 0 ? -q : 0, hi = wsC - q < left ? wsC - q : left;
+  lo = lo > E ? E : lo;
+  hi = clampi(hi, 0, E);
+  if (!ok || lo >= hi) return fixup(0, 0, 0);
+  return fixup(o - clampi(o, 0, total - E), lo, hi);
+}
+
+// Rows = output pixels, k = (filter row, run): forward x, and dy of backward
+// data (whose runs are the filter's mirrored).
+template <class T, int W, int L>
+struct RunRowsLoader {
+  static constexpr bool KC = true, ANY_STEP = true, RUNS = false;
+  static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
+  static_assert(L == 1 || L % 2 == 0, "a lane's k within a step depends on its load's parity");
+  static constexpr int P = L >= 2 ? 2 : 1;
+  typedef RunArgs Args;
+  const char* p;
+  int32_t total, rows, len, lp, hs, wsC, k0;
+  uint32_t magic;
+  int32_t base[L], iy[L], jc[L], kc[P];
+
+  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
+    p = (const char*)a.p, total = a.total, rows = a.rows, len = a.L, lp = a.Lp, hs = a.hs, wsC = a.wsC;
+    magic = a.magic_lp, k0 = (int32_t)kb;
+    const int32_t hw = a.ho * a.wo;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const LoadPos q = load_pos<T, true, W, L>(wave, lane, i);
+      if (i < P) kc[i] = q.c;
+      const int64_t m = mn0 + q.r;
+      if (m < a.M) {
+        const int32_t mi = (int32_t)m, n = mi / hw, rem = mi - n * hw, i0 = rem / a.wo, j0 = rem - i0 * a.wo;
+        iy[i] = i0 - a.padr;
+        jc[i] = (j0 - a.pads) * a.C;
+        base[i] = (n * a.hs + iy[i]) * a.wsC + jc[i];
+      } else {
+        iy[i] = -(1 << 20);  // outside the image for every filter row
+        jc[i] = 0;
+        base[i] = 0;
+      }
+    }
+  }
+  __device__ __forceinline__ void where(int t, int par, int& r, int& e) {
+    const uint32_t k = (uint32_t)(k0 + t * BK + kc[par]);
+    r = (int)fast_div(k, magic);
+    e = (int)k - r * lp;
+  }
+  template <bool CHECK>
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+    int r[P], e[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) where(t, q, r[q], e[q]);
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const int o = clampi(base[i] + r[i % P] * wsC + e[i % P], 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+    }
+  }
+  __device__ __forceinline__ bool plain(int) { return false; }
+  __device__ __forceinline__ uint32_t fx(int t, int i) {
+    int r, e;
+    where(t, i % P, r, e);
+    return run_fix<E>(r < rows && (uint32_t)(iy[i] + r) < (uint32_t)hs, base[i] + r * wsC + e, total, jc[i] + e, wsC,
+                      len - e);
+  }
+};
+
+// The filter [filters][rows][L], K-contiguous with padded runs (forward).
+template <class T, int W, int L>
+struct RunFilterLoader {
+  static constexpr bool KC = true, ANY_STEP = true, RUNS = false;
+  static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
+  static constexpr int P = L >= 2 ? 2 : 1;
+  typedef RunArgs Args;
+  const char* p;
+  int32_t total, rows, len, lp, k0;
+  uint32_t magic;
+  int32_t base[L], kc[P];
+
+  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
+    p = (const char*)a.p, total = a.total, rows = a.rows, len = a.L, lp = a.Lp, magic = a.magic_lp, k0 = (int32_t)kb;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const LoadPos q = load_pos<T, true, W, L>(wave, lane, i);
+      if (i < P) kc[i] = q.c;
+      int64_t m = mn0 + q.r;
+      if (m >= a.M) m = a.M - 1;
+      base[i] = (int32_t)m * a.rows * a.L;
+    }
+  }
+  __device__ __forceinline__ void where(int t, int par, int& r, int& e) {
+    const uint32_t k = (uint32_t)(k0 + t * BK + kc[par]);
+    r = (int)fast_div(k, magic);
+    e = (int)k - r * lp;
+  }
+  template <bool CHECK>
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+    int r[P], e[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) where(t, q, r[q], e[q]);
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const int o = clampi(base[i] + r[i % P] * len + e[i % P], 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+    }
+  }
+  __device__ __forceinline__ bool plain(int) { return false; }
+  __device__ __forceinline__ uint32_t fx(int t, int i) {
+    int r, e;
+    where(t, i % P, r, e);
+    return run_fix<E>(r < rows, base[i] + r * len + e, total, 0, E, len - e);
+  }
+};
+
+// The filter [filters][rows][S][C] of backward data as the MN-contiguous
+// operand: k = (mirrored row, run of (mirrored tap, filter)), columns C.
+// L here is S * filters.
+template <class T, int W, int L>
+struct RunFilterTLoader {
+  static constexpr bool KC = false, ANY_STEP = true, RUNS = false;
+  static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
+  typedef RunArgs Args;  // C: columns; hs: filters; wsC: taps per row (S); magic_a: of the filters
+  const char* p;
+  int32_t total, rows, len, lp, nf, S, C, k0;
+  uint32_t magic, magic_f;
+  int32_t col[L], krow[L];
+
+  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
+    p = (const char*)a.p, total = a.total, rows = a.rows, len = a.L, lp = a.Lp, nf = a.hs, S = a.wsC, C = a.C;
+    magic = a.magic_lp, magic_f = a.magic_a, k0 = (int32_t)kb;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const LoadPos q = load_pos<T, false, W, L>(wave, lane, i);
+      const int64_t mn = mn0 + q.c;
+      col[i] = mn < a.C ? (int32_t)mn : 0;
+      krow[i] = q.r;
+    }
+  }
+  __device__ __forceinline__ bool where(int t, int i, int& o) {
+    const uint32_t k = (uint32_t)(k0 + t * BK + krow[i]);
+    const int r = (int)fast_div(k, magic), e = (int)k - r * lp;
+    const int s = (int)fast_div((uint32_t)e, magic_f), f = e - s * nf;
+    o = ((f * rows + rows - 1 - r) * S + S - 1 - s) * C + col[i];
+    return r < rows && e < len;
+  }
+  template <bool CHECK>
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      int o;
+      where(t, i, o);
+      o = clampi(o, 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+    }
+  }
+  __device__ __forceinline__ bool plain(int) { return false; }
+  __device__ __forceinline__ uint32_t fx(int t, int i) {
+    int o;
+    const bool ok = where(t, i, o);
+    return ok ? fixup(o - clampi(o, 0, total - E), 0, E) : fixup(0, 0, 0);
+  }
+};
+
+// Shifted image columns of the filter gradient: k = output pixel, columns =
+// (filter row, padded run).
+template <class T, int W, int L>
+struct RunColsLoader {
+  static constexpr bool KC = false, ANY_STEP = true, RUNS = true;
+  static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
+  typedef RunArgs Args;
+  const char* p;
+  int32_t total, hs, wsC, C, ho, wo, k0, kend;
+  uint32_t magic_w, magic_h;
+  int32_t krow[L], dy[L], dq[L], left[L];  // filter row, run position (both less the padding), elements left in the run
+
+  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t ke, int wave, int lane) {
+    p = (const char*)a.p, total = a.total, hs = a.hs, wsC = a.wsC, C = a.C, ho = a.ho, wo = a.wo;
+    magic_w = a.magic_a, magic_h = a.magic_b, k0 = (int32_t)kb, kend = (int32_t)ke;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const LoadPos q = load_pos<T, false, W, L>(wave, lane, i);
+      const int32_t nn = (int32_t)mn0 + q.c, r = nn / a.Lp, e = nn - r * a.Lp;
+      krow[i] = q.r;
+      dy[i] = r < a.rows ? r - a.padr : -(1 << 20);
+      dq[i] = e - a.pads * a.C;
+      left[i] = a.L - e;
+    }
+  }
+  __device__ __forceinline__ bool where(int t, int i, int& o, int& q) {
+    const uint32_t px = (uint32_t)(k0 + t * BK + krow[i]);
+    const uint32_t q1 = fast_div(px, magic_w), q2 = fast_div(q1, magic_h);
+    const int y = (int)(q1 - q2 * (uint32_t)ho) + dy[i];
+    q = (int)(px - q1 * (uint32_t)wo) * C + dq[i];
+    o = (int)((q2 * (uint32_t)hs + (uint32_t)y) * (uint32_t)wsC + (uint32_t)q);  // (used only inside the image)
+    return (int)px < kend && (uint32_t)y < (uint32_t)hs;
+  }
+  template <bool CHECK>
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      int o, q;
+      const bool ok = where(t, i, o, q);
+      o = ok ? clampi(o, 0, total - E) : 0;
+      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+    }
+  }
+  __device__ __forceinline__ bool plain(int) { return false; }
+  __device__ __forceinline__ uint32_t fx(int t, int i) {
+    int o, q;
+    const bool ok = where(t, i, o, q);
+    return run_fix<E>(ok, o, total, q, wsC, left[i]);
+  }
+};
+
+// ------------------------------------------------------------- fragments
+
+template <class T, bool KC, int W>
+__device__ __forceinline__ lds::LaneFrag lane_frag(int lane) {
+  if constexpr (KC || sizeof(typename T::storage) == 2) {
+    return lds::lane_frag<KC, W>(lane);
+  } else {
+    lds::LaneFrag f;
+    f.swz = (uint32_t)(lane >> 4);
+    f.row_off = (uint32_t)(lane >> 4) * (4u * W * 4u) + (uint32_t)(lane & 15) * 4u;
+    f.c = 0;
+    return f;
+  }
+}
+
+// 16 rows (mn) from tile row r0, half step kk (0 or 1): 32 16-bit or 16 fp32 k.
+template <class T, bool KC, int W>
+__device__ __forceinline__ uint4 fragment(const char* tile, int r0, int kk, const lds::LaneFrag& f) {
+  if constexpr (KC || sizeof(typename T::storage) == 2) {
+    return lds::fragment<KC, W>(tile, r0, kk, f);
+  } else {
+    const char* p = tile + (uint32_t)kk * (16u * W * 4u) + f.row_off + (((uint32_t)(r0 >> 4) ^ f.swz) << 6);
+    return make_uint4(*(const uint32_t*)p, *(const uint32_t*)(p + W * 4), *(const uint32_t*)(p + 2 * W * 4),
+                      *(const uint32_t*)(p + 3 * W * 4));
+  }
+}
+
+__device__ __forceinline__ uint32_t dword(const uint4& v, int q) {
+  return q == 0 ? v.x : q == 1 ? v.y : q == 2 ? v.z : v.w;
+}
+
+// NA accumulator sets (fp32: 1 or 4, set q for k mod 4 = q).
+template <class T, int NA, int FM, int FN>
+__device__ __forceinline__ void mfma_step(const uint4 (&a)[FM], const uint4 (&b)[FN], float4_t (&acc)[NA][FM][FN]) {
+  if constexpr (sizeof(typename T::storage) == 2) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[0][i][j] = Mfma<T>::run(b[j], a[i], acc[0][i][j]);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[q % NA][i][j] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, dword(b[j], q)),
+                                                   __builtin_bit_cast(float, dword(a[i], q)), acc[q % NA][i][j], 0, 0, 0);
+  }
+}
+
+template <class T, class TL, int NR>
+struct Sets {
+  uint4 a[NR][TL::LA], b[NR][TL::LB];
+};
+
+// Tile t of one operand: registers -> LDS.
+template <int ES, bool CHECK, class Loader, int L>
+__device__ __forceinline__ void commit(char* dst, int t, const uint4 (&v)[L], Loader& ld) {
+  if constexpr (Loader::ANY_STEP) {
+    // image edges turn up in any step: test this wave's chunks
+    uint32_t fx[L];
+    bool need = false;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      fx[i] = ld.fx(t, i);
+      need |= fx[i] != fixup(0, 0, 16 / ES);
+    }
+    if (__any(need)) {
+#pragma unroll
+      for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = apply_fix<ES>(v[i], fx[i]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = v[i];
+    }
+  } else if (!CHECK || ld.plain(t)) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = v[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = apply_fix<ES>(v[i], ld.fx(t, i));
+  }
+}
+
+// Steps t + J .. t + U - 1 of one unrolled round; tile t + J is in LDS stage
+// J % 2, the tiles after it in register sets (J + 1) % NR, ...
+// CHECK = false: every tile loaded in the round comes before the last one.
+template <class T, class TL, int NR, class LA, class LB, int J, int U, bool CHECK, int NA>
+__device__ __forceinline__ void steps(int t, int nk, char* const (&sa)[2], char* const (&sb)[2], uint32_t wa,
+                                      uint32_t wb, int wm, int wn, const lds::LaneFrag& fa, const lds::LaneFrag& fb,
+                                      LA& la, LB& lb, Sets<T, TL, NR>& s, float4_t (&acc)[NA][TL::FM][TL::FN]) {
+  if constexpr (J < U) {
+    if (CHECK && t + J >= nk) return;
+    constexpr int S = J % NR, S1 = (J + 1) % NR;
+    if (!CHECK || t + J + NR < nk) {
+      la.template load<CHECK>(t + J + NR, s.a[S]);
+      lb.template load<CHECK>(t + J + NR, s.b[S]);
+    }
+    const char* ta = sa[J & 1];
+    const char* tb = sb[J & 1];
+    uint4 a0[TL::FM], b0[TL::FN], a1[TL::FM], b1[TL::FN];
+#pragma unroll
+    for (int i = 0; i < TL::FM; ++i) a0[i] = fragment<T, LA::KC, TL::BM>(ta, wm * TL::WTM + i * 16, 0, fa);
+#pragma unroll
+    for (int j = 0; j < TL::FN; ++j) b0[j] = fragment<T, LB::KC, TL::BN>(tb, wn * TL::WTN + j * 16, 0, fb);
+#pragma unroll
+    for (int i = 0; i < TL::FM; ++i) a1[i] = fragment<T, LA::KC, TL::BM>(ta, wm * TL::WTM + i * 16, 1, fa);
+#pragma unroll
+    for (int j = 0; j < TL::FN; ++j) b1[j] = fragment<T, LB::KC, TL::BN>(tb, wn * TL::WTN + j * 16, 1, fb);
+    mfma_step<T, NA>(a0, b0, acc);
+    mfma_step<T, NA>(a1, b1, acc);
+    if (!CHECK || t + J + 1 < nk) {
+      commit<El<T>::ES, CHECK>(sa[(J + 1) & 1] + wa, t + J + 1, s.a[S1], la);
+      commit<El<T>::ES, CHECK>(sb[(J + 1) & 1] + wb, t + J + 1, s.b[S1], lb);
+    }
+    __syncthreads();
+    steps<T, TL, NR, LA, LB, J + 1, U, CHECK, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, acc);
+  }
+}
+
+template <class T, class OutT, class TL, int NR, class LA, class LB>
+__global__ void __launch_bounds__(TL::NT, TL::OCC)
+gemm_reg_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N, int64_t K, Epilogue ep) {
+  constexpr int FM = TL::FM, FN = TL::FN, ES = El<T>::ES, BK = El<T>::BK;
+  __shared__ __attribute__((aligned(1024))) char a0[TL::A_BYTES];
+  __shared__ __attribute__((aligned(1024))) char b0[TL::B_BYTES];
+  __shared__ __attribute__((aligned(1024))) char a1[TL::A_BYTES];
+  __shared__ __attribute__((aligned(1024))) char b1[TL::B_BYTES];
+  char* const sa[2] = {a0, a1};
+  char* const sb[2] = {b0, b1};
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / TL::WN, wn = wave % TL::WN;
+
+  int tm, tn, split;
+  split_tile_coords(ceil_div(M, TL::BM), ceil_div(N, TL::BN), tm, tn, split);
+  const int64_t m0 = (int64_t)tm * TL::BM, n0 = (int64_t)tn * TL::BN;
+  int64_t kbeg = 0, kend = K;
+  if (ep.partial) {
+    kbeg = (int64_t)split * ep.k_per_split;
+    kend = kbeg + ep.k_per_split < K ? kbeg + ep.k_per_split : K;
+  }
+  const int nk = (int)ceil_div(kend - kbeg, BK);
+
+  LA la;
+  LB lb;
+  la.init(aa, m0, kbeg, kend, wave, lane);
+  lb.init(ba, n0, kbeg, kend, wave, lane);
+  const uint32_t wa = (uint32_t)(wave * TL::LA) * 1024u + (uint32_t)lane * 16u;
+  const uint32_t wb = (uint32_t)(wave * TL::LB) * 1024u + (uint32_t)lane * 16u;
+  const lds::LaneFrag fa = lane_frag<T, LA::KC, TL::BM>(lane), fb = lane_frag<T, LB::KC, TL::BN>(lane);
+
+  // fp32 sums of a wave tile of few fragments run in four chains (k mod 4)
+  // that are added at the end: a quarter of the roundings in a row, and
+  // enough independent MFMAs to hide their latency
+  constexpr int NA = ES == 4 && FM * FN <= 4 ? 4 : 1;
+  float4_t accs[NA][FM][FN];
+#pragma unroll
+  for (int q = 0; q < NA; ++q)
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) accs[q][i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
+
+  Sets<T, TL, NR> s;
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+    if (r < nk) {
+      la.template load<true>(r, s.a[r]);
+      lb.template load<true>(r, s.b[r]);
+    }
+  if (nk > 0) {
+    commit<ES, true>(sa[0] + wa, 0, s.a[0], la);
+    commit<ES, true>(sb[0] + wb, 0, s.b[0], lb);
+  }
+  __syncthreads();
+  constexpr int U = NR % 2 == 0 ? NR : 2 * NR;
+  int t = 0;
+  for (; t + U + NR < nk; t += U)
+    steps<T, TL, NR, LA, LB, 0, U, false, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);
+  for (; t < nk; t += U)
+    steps<T, TL, NR, LA, LB, 0, U, true, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);
+  float4_t(&acc)[FM][FN] = accs[0];
+  if constexpr (NA == 4) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[i][j] = (accs[0][i][j] + accs[1][i][j]) + (accs[2][i][j] + accs[3][i][j]);
+  }
+
+  const int64_t mb = m0 + wm * TL::WTM + (lane & 15);
+  const int64_t nb = n0 + wn * TL::WTN + 4 * (lane >> 4);
+  if constexpr (LB::RUNS) {
+    // filter gradients: columns run through padded filter rows (Lp columns
+    // for L elements); plain fp32 results or split partials
+    const int64_t NR_ = (int64_t)ba.rows * ba.L;
+    float* P = ep.partial ? ep.partial + (int64_t)split * M * NR_ : (float*)ep.D;
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int32_t n = (int32_t)(nb + j * 16), r = n / ba.Lp, e = n - r * ba.Lp;
+      if (n >= N) continue;
+      const bool v4 = (ba.L & 3) == 0 && ((uintptr_t)P & 15) == 0 && e + 4 <= ba.L;
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        const int64_t m = mb + i * 16;
+        if (m >= M) continue;
+        float* p = P + m * NR_ + (int64_t)r * ba.L + e;
+        if (v4) {
+          *(float4*)p = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (e + q < ba.L) p[q] = acc[i][j][q];
+        }
+      }
+    }
+    return;
+  }
+  if (ep.partial) {
+    float* P = ep.partial + (int64_t)split * M * N;
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int64_t m = mb + i * 16, n = nb + j * 16;
+        if (m >= M) continue;
+        float* p = P + m * N + n;
+        if ((N & 3) == 0 && n + 4 <= N) {
+          *(float4*)p = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (n + e < N) p[e] = acc[i][j][e];
+        }
+      }
+    return;
+  }
+  if (full_tile_epilogue(ep, m0 + TL::BM <= M && n0 + TL::BN <= N, N)) {
+    if constexpr (ES == 2) {
+      epilogue_interior<T, OutT, FM, FN>(ep, M, N, mb, nb, acc);
+    } else {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) epilogue_store4<T, OutT, true>(ep, M, N, mb + i * 16, nb + j * 16, acc[i][j]);
+    }
+    return;
+  }
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) epilogue_store4<T, OutT>(ep, M, N, mb + i * 16, nb + j * 16, acc[i][j]);
+}
+
+// 128 x 128 with waves of 64 x 64; 128 x 64 and 64 x 64 for narrow products
+// and small grids
+typedef lds::Tile<128, 128, 2, 2, 2> TileR128;
+typedef lds::Tile<128, 64, 2, 2, 2> TileR128x64;
+typedef lds::Tile<64, 64, 2, 2, 2> TileR64;
+
+}  // namespace reg
+}  // namespace mdnn

@@ -1,0 +1,68 @@
+// Plain-matrix products on the register-staged mainloop (gemm_reg.h).
+#include "gemm_reg.h"
+
+#include "internal.h"
+
+namespace mdnn {
+
+namespace {
+
+template <class T, class OutT, class TL, int NR, bool A_KC, bool B_KC>
+void launch(const reg::MatArgs& a, const reg::MatArgs& b, int64_t M, int64_t N, int64_t K, const Epilogue& ep,
+            int splits, hipStream_t st) {
+  const dim3 grid((unsigned)(ceil_div(M, TL::BM) * ceil_div(N, TL::BN)), (unsigned)splits);
+  hipLaunchKernelGGL((reg::gemm_reg_kernel<T, OutT, TL, NR, reg::MatLoader<T, A_KC, TL::BM, TL::LA>,
+                                           reg::MatLoader<T, B_KC, TL::BN, TL::LB>>),
+                     grid, dim3(TL::NT), 0, st, a, b, M, N, K, ep);
+}
+
+// 128 x 128 tiles from one per CU on, else 64 x 64 (four times the
+// workgroups, four register sets: their steps are shorter than a load).
+template <class T, class OutT, bool A_KC, bool B_KC>
+void run(const reg::MatArgs& a, const reg::MatArgs& b, int64_t M, int64_t N, int64_t K, const Epilogue& ep,
+         int splits, hipStream_t st) {
+  if (M > 64 && N > 64 && ceil_div(M, 128) * ceil_div(N, 128) * splits >= 256)
+    launch<T, OutT, reg::TileR128, 2, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
+  else
+    launch<T, OutT, reg::TileR64, 4, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
+}
+
+template <class T, class OutT>
+void run_layout(mdnn_layout_t layout, const reg::MatArgs& a, const reg::MatArgs& b, int64_t M, int64_t N, int64_t K,
+                const Epilogue& ep, int splits, hipStream_t st) {
+  if (layout == MDNN_NN) run<T, OutT, true, false>(a, b, M, N, K, ep, splits, st);
+  else if (layout == MDNN_NT) run<T, OutT, true, true>(a, b, M, N, K, ep, splits, st);
+  else run<T, OutT, false, false>(a, b, M, N, K, ep, splits, st);
+}
+
+// one operand: chunks of 16 bytes along its contiguous dimension lie inside
+// it, byte offsets (within the operand, or within one K step) in 32 bits
+bool operand_ok(int64_t es, bool kc, int64_t MN, int64_t ld, int64_t K) {
+  const int64_t e = 16 / es, bk = 128 / es;
+  if (kc) return K >= e && (MN - 1) * ld + K < ((int64_t)1 << 32) / es;
+  return MN >= e && bk * ld + MN < ((int64_t)1 << 32) / es;
+}
+
+}  // namespace
+
+bool gemm_reg_ok(mdnn_dtype_t ab, mdnn_layout_t layout, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb,
+                 int splits) {
+  const int64_t es = (int64_t)dtype_size(ab);
+  return M > 0 && N > 0 && K > 0 && operand_ok(es, layout != MDNN_TN, M, lda, K) &&
+         operand_ok(es, layout == MDNN_NT, N, ldb, K) && ceil_div(M, 64) * ceil_div(N, 64) <= 0x7fffffffLL &&
+         K <= 0x7fffffffLL && splits <= 65535;
+}
+
+mdnn_status_t gemm_reg(mdnn_dtype_t ab, mdnn_dtype_t d, mdnn_layout_t layout, int64_t M, int64_t N, int64_t K,
+                       const void* A, int64_t lda, const void* B, int64_t ldb, const Epilogue& ep, int splits,
+                       hipStream_t st) {
+  const reg::MatArgs a{A, lda, M, K}, b{B, ldb, N, K};
+  if (ab == MDNN_F32) run_layout<F32, F32>(layout, a, b, M, N, K, ep, splits, st);
+  else if (ab == MDNN_F16 && d == MDNN_F32) run_layout<F16, F32>(layout, a, b, M, N, K, ep, splits, st);
+  else if (ab == MDNN_F16) run_layout<F16, F16>(layout, a, b, M, N, K, ep, splits, st);
+  else if (d == MDNN_F32) run_layout<BF16, F32>(layout, a, b, M, N, K, ep, splits, st);
+  else run_layout<BF16, BF16>(layout, a, b, M, N, K, ep, splits, st);
+  return check_launch("gemm_reg_kernel");
+}
+
+}  // namespace mdnn
