@@ -7,6 +7,7 @@
 
 #include "conv_halo.h"
 #include "conv_pipe.h"
+#include "conv_reg.h"
 #include "conv_small.h"
 #include "gemm_launch.h"
 
@@ -141,6 +142,7 @@ extern "C" mdnn_status_t mdnn_conv2d_fwd(const mdnn_conv_shape_t* shape, const v
     if (halo_allowed()) MDNN_TRY(conv_halo(g, false, x, w, ep, io_type, y_type, st, &done));
     if (done) return MDNN_SUCCESS;
     MDNN_TRY(conv_pipe_fwd(g, x, w, ep, io_type, y_type, st, &done));
+    if (!done) MDNN_TRY(conv_reg_fwd(g, x, w, ep, io_type, y_type, st, &done));
     if (done) return MDNN_SUCCESS;
   }
   switch (io_type) {
@@ -175,6 +177,7 @@ extern "C" mdnn_status_t mdnn_conv2d_bwd_data(const mdnn_conv_shape_t* shape, co
     if (halo_allowed()) MDNN_TRY(conv_halo(g, true, dy, w, ep, io_type, dx_type, st, &done));
     if (done) return MDNN_SUCCESS;
     MDNN_TRY(conv_pipe_bwd_data(g, dy, w, ep, io_type, dx_type, st, &done));
+    if (!done) MDNN_TRY(conv_reg_bwd_data(g, dy, w, ep, io_type, dx_type, st, &done));
     if (done) return MDNN_SUCCESS;
   }
   switch (io_type) {
@@ -187,11 +190,13 @@ extern "C" mdnn_status_t mdnn_conv2d_bwd_data(const mdnn_conv_shape_t* shape, co
 // Workspace: split-K partials of dw (room for the pipelined kernel's plan and
 // the general kernel's, whichever runs), then (256-byte aligned) the partial
 // column sums of db.
-static size_t filter_ws_split_bytes(const ConvGeom& g) {
+static size_t filter_ws_split_bytes(const ConvGeom& g, mdnn_dtype_t io) {
   const size_t mn = (size_t)g.k * ((size_t)g.r * g.s * g.c) * sizeof(float);
   const SplitPlan p = filter_plan(g), q = conv_pipe_filter_plan(g);
   size_t splits = p.splits > 1 ? (size_t)p.splits : 0;
   if (q.splits > 1 && (size_t)q.splits > splits) splits = (size_t)q.splits;
+  const SplitPlan u = conv_reg_filter_plan(g, io);
+  if (u.splits > 1 && (size_t)u.splits > splits) splits = (size_t)u.splits;
   // the vector-ALU kernels' block count (at least the matrix-core kernel's)
   const int64_t sb = conv_small_filter_blocks(g, MDNN_F32);
   if (sb > 0 && (size_t)sb > splits) splits = (size_t)sb;
@@ -203,7 +208,7 @@ extern "C" size_t mdnn_conv2d_bwd_filter_workspace(const mdnn_conv_shape_t* shap
                                                    mdnn_dtype_t io_type) {
   ConvGeom g;
   if (check_conv_shape(shape, g) != MDNN_SUCCESS || !dtype_ok(io_type)) return 0;
-  return filter_ws_split_bytes(g) + column_sums_ws_bytes((int64_t)g.n * g.ho * g.wo, g.k);
+  return filter_ws_split_bytes(g, io_type) + column_sums_ws_bytes((int64_t)g.n * g.ho * g.wo, g.k);
 }
 
 // Workspace of mdnn_conv2d_bwd_filter_noalloc: one fixed array per GPU, held
@@ -284,6 +289,8 @@ mdnn_status_t mdnn::conv2d_bwd_filter_deferred(const mdnn_conv_shape_t* shape, c
   }
   if (!done && pipe_allowed())
     MDNN_TRY(conv_pipe_bwd_filter(g, x, dy, dw, workspace, io_type, st, &done, defer));
+  if (!done && pipe_allowed())
+    MDNN_TRY(conv_reg_bwd_filter(g, x, dy, dw, workspace, io_type, st, &done, defer));
   if (!done) {
     switch (io_type) {
       case MDNN_F16: MDNN_TRY(bwd_filter_impl<F16>(g, x, dy, dw, workspace, st, defer)); break;
@@ -292,7 +299,7 @@ mdnn_status_t mdnn::conv2d_bwd_filter_deferred(const mdnn_conv_shape_t* shape, c
     }
   }
   if (db) {
-    const size_t off = filter_ws_split_bytes(g);
+    const size_t off = filter_ws_split_bytes(g, io_type);
     const size_t cs = column_sums_ws_bytes((int64_t)g.n * g.ho * g.wo, g.k);
     return column_sums(dy, nullptr, io_type, (int64_t)g.n * g.ho * g.wo, g.k, db,
                        cs ? (char*)workspace + off : nullptr, cs, st, defer);

@@ -1,0 +1,68 @@
+"""Convolutions on the register-staged kernel: fp32 data and channel counts
+that are no multiple of 8, at the edges of its runs (one filter row of
+s * c elements, padded to 8 16-bit or 4 fp32 ones), tiles and K steps, all
+three passes against the oracle; NaN around every operand must not reach a
+result."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import ops
+from oracle.rounding import decode
+from tests.helpers import DT, accum_bound, dev, host64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def mdnn():
+    import torch
+    torch.cuda.set_device(0)
+    import paper_2011_11188_amd as m
+    return m
+
+
+# (n, h, w, c_in, c_out, r, s, pad): three channels with wide filters (runs of
+# 21, 15, 9), a run one over and one under a chunk, channels either side of 64
+# and 128, one-pixel-wide images, valid and over-wide padding, r != s, a
+# tall output (128 x 64 tiles), split filter gradients with a ragged last step.
+SHAPES = [
+    (2, 11, 9, 3, 64, 7, 7, 3), (3, 8, 8, 3, 70, 5, 5, 2), (2, 6, 7, 3, 130, 3, 3, 1), (5, 13, 11, 17, 33, 3, 3, 1),
+    (2, 7, 5, 65, 67, 3, 3, 0), (1, 9, 1, 20, 129, 3, 3, 1), (2, 5, 6, 12, 9, 1, 1, 0), (2, 4, 5, 100, 12, 1, 5, 2),
+    (3, 6, 6, 10, 11, 2, 4, 3), (2, 180, 190, 7, 60, 3, 3, 1), (4, 30, 31, 5, 13, 3, 3, 1),
+]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_conv_any_channels(mdnn, shape, dt):
+    import torch
+    n, h, w, ci, co, r, s, pad = shape
+    ho, wo = h + 2 * pad - r + 1, w + 2 * pad - s + 1
+    arr = {"x": W.normal((n, h, w, ci), 61, 1, dt), "w": W.normal((co, r, s, ci), 61, 2, dt),
+           "dy": W.normal((n, ho, wo, co), 61, 3, dt)}
+    val = {k: decode(v, dt) for k, v in arr.items()}
+    mag = {k: np.abs(v) for k, v in val.items()}
+    buf, t = {}, {}
+    for k, v in arr.items():     # each operand one element into a buffer of NaN
+        d = dev(v, dt).reshape(-1)
+        buf[k] = torch.full((d.numel() + 2,), float("nan"), dtype=d.dtype, device="cuda")
+        t[k] = buf[k][1:-1]
+        t[k].copy_(d)
+    sh = mdnn.ConvShape(n, h, w, ci, co, r, s, pad)
+    y = torch.full((n, ho, wo, co), float("nan"), device="cuda")
+    dx = torch.full((n, h, w, ci), float("nan"), device="cuda")
+    dw, db = torch.full((co, r, s, ci), float("nan"), device="cuda"), torch.empty(co, device="cuda")
+    ws = torch.full((max(mdnn.mdnn_conv2d_bwd_filter_workspace(sh, DT[dt]), 256),), 255, dtype=torch.uint8, device="cuda")
+    mdnn.mdnn_conv2d_fwd(sh, t["x"], t["w"], DT[dt], None, 0, y, DT["f32"])
+    mdnn.mdnn_conv2d_bwd_data(sh, t["dy"], t["w"], DT[dt], None, dx, DT["f32"])
+    mdnn.mdnn_conv2d_bwd_filter(sh, t["x"], t["dy"], DT[dt], dw, db, ws, ws.numel())
+    for name, got, want, size, k in (
+            ("y", y, ops.conv2d_fwd(val["x"], val["w"], pad), ops.conv2d_fwd(mag["x"], mag["w"], pad), r * s * ci),
+            ("dx", dx, ops.conv2d_bwd_data(val["dy"], val["w"], pad, h, w),
+             ops.conv2d_bwd_data(mag["dy"], mag["w"], pad, h, w), r * s * co),
+            ("dw", dw, ops.conv2d_bwd_filter(val["x"], val["dy"], pad, r, s),
+             ops.conv2d_bwd_filter(mag["x"], mag["dy"], pad, r, s), n * ho * wo),
+            ("db", db, val["dy"].sum((0, 1, 2)), mag["dy"].sum((0, 1, 2)), n * ho * wo)):
+        err = np.abs(host64(got) - want)
+        assert np.all(err <= accum_bound(size, k + 1)), (name, shape, dt, float(np.nanmax(err)), bool(np.isnan(err).any()))
