@@ -31,6 +31,11 @@ typedef lds::Tile<64, 128, 2, 2, 4> TileFlat;
 typedef lds::Tile<64, 128, 2, 4, 2> TileFiltN;
 typedef lds::Tile<64, 64, 2, 2, 4> TileFiltS;
 
+// 256 x 64 tiles: narrow outputs, and those whose last 128 columns would be
+// at most half used while 256-row tiles still fill the chip
+bool narrow_tiles(int64_t M, int64_t N) {
+  return N <= 64 || ((N - 1) % 128 < 64 && ceil_div(M, 256) * ceil_div(N, 64) >= 256);
+}
 // 128 x 128 tiles fill fewer than 256 workgroups: the 64 x 128 tile instead
 bool flat_tiles(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, 128) < 256; }
 constexpr int FILTER_STAGES = 3;
@@ -77,36 +82,55 @@ mdnn_status_t rows_typed(const lds::ConvRowsArgs& a, const void* w, int32_t ldw,
 
 }  // namespace
 
-// Forward with c_in % 32 == 0 (not 64): K padded to whole steps of two
-// 32-channel half blocks, the filter read range-checked.
-template <class T, class OutT>
-mdnn_status_t rows32_dispatch(const lds::ConvRowsArgs& a, const lds::MatRCArgs& b, int64_t M, int64_t N, int64_t Kp,
-                              const Epilogue& ep, hipStream_t st) {
-  if (N <= 64)
-    return run_pipe<T, OutT, TileTall, 2, lds::ConvRows32Loader<256, TileTall::LA>,
-                    lds::MatLoaderRC<64, TileTall::LB>>(a, b, M, N, Kp, ep, 1, st);
-  return run_pipe<T, OutT, TileSquare, 2, lds::ConvRows32Loader<128, TileSquare::LA>,
-                  lds::MatLoaderRC<128, TileSquare::LB>>(a, b, M, N, Kp, ep, 1, st);
+// Channel counts that are a multiple of 8 but not of 64 (the per-tap loaders
+// above take 64): forward (B: the filter, range-checked) and backward data
+// (B: TapRowsLoader).
+namespace {
+
+template <class T, class OutT, class TL, bool BWD>
+mdnn_status_t run_runs8(const lds::ConvRunsArgs& a, const ConvGeom& g, const void* w, int64_t M, int64_t N, int64_t K,
+                        const Epilogue& ep, hipStream_t st) {
+  typedef lds::ConvRuns8Loader<TL::BM, TL::LA> LA;
+  const uint32_t w_bytes = (uint32_t)((int64_t)g.k * g.r * g.s * g.c * 2);
+  if constexpr (!BWD) {
+    const lds::MatRCArgs b{w, w_bytes, K, N, K};
+    return run_pipe<T, OutT, TL, 2, LA, lds::MatLoaderRC<true, TL::BN, TL::LB>>(a, b, M, N, K, ep, 1, st);
+  } else {
+    const lds::TapRowsArgs b{w, w_bytes, g.k, g.r * g.s, g.c, magic_of((uint32_t)g.k)};
+    return run_pipe<T, OutT, TL, 2, LA, lds::TapRowsLoader<TL::BN, TL::LB>>(a, b, M, N, K, ep, 1, st);
+  }
 }
 
-mdnn_status_t conv_pipe_fwd32(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, mdnn_dtype_t io,
-                              mdnn_dtype_t out, hipStream_t st, bool* done) {
-  const int64_t M = (int64_t)g.n * g.ho * g.wo, N = g.k, K = (int64_t)g.r * g.s * g.c;
-  const int64_t x_bytes = (int64_t)g.n * g.h * g.w * g.c * 2, w_bytes = N * K * 2;
-  if (x_bytes > BUF_MAX || w_bytes > BUF_MAX || M > BUF_MAX) return MDNN_SUCCESS;
-  const int64_t Kp = ceil_div(K, (int64_t)lds::BK) * lds::BK;
-  lds::ConvRowsArgs a{x, (uint32_t)x_bytes, g.h, g.w, g.c, g.ho, g.wo, g.s, g.pad, 0, M};
-  a.r = g.r;
-  const lds::MatRCArgs b{w, (uint32_t)w_bytes, K, N};
+template <class T, class OutT, bool BWD>
+mdnn_status_t runs8_dispatch(const lds::ConvRunsArgs& a, const ConvGeom& g, const void* w, int64_t M, int64_t N,
+                             int64_t K, const Epilogue& ep, hipStream_t st) {
+  if (narrow_tiles(M, N)) return run_runs8<T, OutT, TileTall, BWD>(a, g, w, M, N, K, ep, st);
+  if (flat_tiles(M, N)) return run_runs8<T, OutT, TileFlat, BWD>(a, g, w, M, N, K, ep, st);
+  return run_runs8<T, OutT, TileSquare, BWD>(a, g, w, M, N, K, ep, st);
+}
+
+// rows over an ho x wo grid gathered from src [n][hs][ws][c]
+template <bool BWD>
+mdnn_status_t conv_pipe_runs8(const ConvGeom& g, const void* src, int32_t hs, int32_t ws, int32_t c, int32_t ho,
+                              int32_t wo, int32_t padr, int32_t pads, const void* w, int64_t N, const Epilogue& ep,
+                              mdnn_dtype_t io, mdnn_dtype_t out, hipStream_t st, bool* done) {
+  const int64_t M = (int64_t)g.n * ho * wo, len = (int64_t)g.s * c, K = g.r * len;
+  const int64_t bytes = (int64_t)g.n * hs * ws * c * 2, w_bytes = (int64_t)g.k * g.r * g.s * g.c * 2;
+  if (bytes > BUF_MAX || w_bytes > BUF_MAX || M > BUF_MAX || (K + 64) * (len > g.k ? len : g.k) >= ((int64_t)1 << 32))
+    return MDNN_SUCCESS;
+  const lds::ConvRunsArgs a{src, (uint32_t)bytes, hs,           ws * c, c,    ho, wo, g.r, (int32_t)len, magic_of((uint32_t)len),
+                            padr, pads,           M};
   if (io == MDNN_F16)
-    MDNN_TRY((out == MDNN_F32 ? rows32_dispatch<F16, F32>(a, b, M, N, Kp, ep, st)
-                              : rows32_dispatch<F16, F16>(a, b, M, N, Kp, ep, st)));
+    MDNN_TRY((out == MDNN_F32 ? runs8_dispatch<F16, F32, BWD>(a, g, w, M, N, K, ep, st)
+                              : runs8_dispatch<F16, F16, BWD>(a, g, w, M, N, K, ep, st)));
   else
-    MDNN_TRY((out == MDNN_F32 ? rows32_dispatch<BF16, F32>(a, b, M, N, Kp, ep, st)
-                              : rows32_dispatch<BF16, BF16>(a, b, M, N, Kp, ep, st)));
+    MDNN_TRY((out == MDNN_F32 ? runs8_dispatch<BF16, F32, BWD>(a, g, w, M, N, K, ep, st)
+                              : runs8_dispatch<BF16, BF16, BWD>(a, g, w, M, N, K, ep, st)));
   *done = true;
   return MDNN_SUCCESS;
 }
+
+}  // namespace
 
 mdnn_status_t conv_pipe_fwd(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep,
                             mdnn_dtype_t io, mdnn_dtype_t out, hipStream_t st, bool* done) {
@@ -114,7 +138,9 @@ mdnn_status_t conv_pipe_fwd(const ConvGeom& g, const void* x, const void* w, con
   const int64_t M = (int64_t)g.n * g.ho * g.wo, N = g.k, K = (int64_t)g.r * g.s * g.c;
   const int64_t x_bytes = (int64_t)g.n * g.h * g.w * g.c * 2;
   if (io == MDNN_F32 || !aligned(x, 16) || !aligned(w, 16)) return MDNN_SUCCESS;
-  if (g.c % 64 != 0) return g.c % 32 == 0 ? conv_pipe_fwd32(g, x, w, ep, io, out, st, done) : MDNN_SUCCESS;
+  if (g.c % 8 != 0) return MDNN_SUCCESS;
+  if (g.c % 64 != 0)
+    return conv_pipe_runs8<false>(g, x, g.h, g.w, g.c, g.ho, g.wo, g.pad, g.pad, w, N, ep, io, out, st, done);
   if (x_bytes > BUF_MAX || M > BUF_MAX || N * K * 2 >= ((int64_t)1 << 32)) return MDNN_SUCCESS;
   const lds::ConvRowsArgs a{x, (uint32_t)x_bytes, g.h, g.w, g.c, g.ho, g.wo, g.s, g.pad, 0, M};
   MDNN_TRY(rows_typed<false>(a, w, (int32_t)K, g, M, N, K, ep, io, out, st));
@@ -127,7 +153,10 @@ mdnn_status_t conv_pipe_bwd_data(const ConvGeom& g, const void* dy, const void* 
   *done = false;
   const int64_t M = (int64_t)g.n * g.h * g.w, N = g.c, K = (int64_t)g.r * g.s * g.k;
   const int64_t dy_bytes = (int64_t)g.n * g.ho * g.wo * g.k * 2;
-  if (io == MDNN_F32 || g.k % 64 != 0 || g.c % 8 != 0 || !aligned(dy, 16) || !aligned(w, 16)) return MDNN_SUCCESS;
+  if (io == MDNN_F32 || g.k % 8 != 0 || g.c % 8 != 0 || !aligned(dy, 16) || !aligned(w, 16)) return MDNN_SUCCESS;
+  if (g.k % 64 != 0)
+    return conv_pipe_runs8<true>(g, dy, g.ho, g.wo, g.k, g.h, g.w, g.r - 1 - g.pad, g.s - 1 - g.pad, w, N, ep, io, out,
+                                 st, done);
   const int64_t ldw = (int64_t)g.r * g.s * g.c;  // filter elements between consecutive c_out
   if (dy_bytes > BUF_MAX || M > BUF_MAX || (64 * ldw + N) * 2 >= ((int64_t)1 << 32)) return MDNN_SUCCESS;
   // rows over the h x w input grid, gathered from the ho x wo grid of dy
@@ -140,9 +169,10 @@ mdnn_status_t conv_pipe_bwd_data(const ConvGeom& g, const void* dy, const void* 
 SplitPlan conv_pipe_filter_plan(const ConvGeom& g) {
   SplitPlan p{0, 0};
   const int64_t M = g.k, N = (int64_t)g.r * g.s * g.c, K = (int64_t)g.n * g.ho * g.wo;
-  const int64_t x_bytes = (int64_t)g.n * g.h * g.w * g.c * 2;
-  if (g.ho != g.h || g.wo != g.w || g.c % 8 != 0 || g.k % 8 != 0 || K % lds::BK != 0 || K == 0) return p;
-  if (x_bytes > BUF_MAX || K * (g.w - 1) >= ((int64_t)1 << 32) || (K / g.w) * (g.h - 1) >= ((int64_t)1 << 32))
+  const int64_t x_bytes = (int64_t)g.n * g.h * g.w * g.c * 2, Kp = ceil_div(K, (int64_t)lds::BK) * lds::BK;
+  if (g.c % 8 != 0 || g.k % 8 != 0 || K == 0) return p;
+  if (x_bytes > BUF_MAX || K * g.k * 2 > BUF_MAX || Kp * (g.wo - 1) >= ((int64_t)1 << 32) ||
+      (Kp / g.wo + 1) * (g.ho - 1) >= ((int64_t)1 << 32))
     return p;
   if (N > BUF_MAX / 4 || M * N > BUF_MAX / 4) return p;
   // aim at about 256 (64 x 128 tiles, 8 waves) or 512 (64 x 64 tiles, 4
@@ -150,7 +180,7 @@ SplitPlan conv_pipe_filter_plan(const ConvGeom& g) {
   // stay within the cap
   const bool narrow = M <= 64;
   const int64_t tiles = narrow ? ceil_div(N, TileFiltN::BN) : ceil_div(M, 64) * ceil_div(N, 64);
-  const int64_t steps = K / lds::BK;
+  const int64_t steps = Kp / lds::BK;
   int64_t s = ceil_div(narrow ? 256 : 512, tiles);
   if (s > steps / 4) s = steps / 4;
   while (s > 1 && (size_t)s * M * N * 4 > FILTER_WS_MAX) --s;
@@ -172,9 +202,8 @@ template <class T, class TL>
 mdnn_status_t filter_run(const ConvGeom& g, const void* x, const void* dy, float* dw, void* ws, const SplitPlan& p,
                          hipStream_t st, ReduceBatch* defer) {
   const int64_t M = g.k, N = (int64_t)g.r * g.s * g.c, K = (int64_t)g.n * g.ho * g.wo;
-  const lds::MatArgs a{dy, g.k, g.k};
-  const lds::ConvColsArgs b{x, (uint32_t)((int64_t)g.n * g.h * g.w * g.c * 2), g.h, g.w, g.c, g.s, g.pad,
-                            magic_of((uint32_t)g.w), magic_of((uint32_t)g.h), N};
+  const lds::ConvColsArgs b{x,    (uint32_t)((int64_t)g.n * g.h * g.w * g.c * 2), g.h, g.w, g.c, g.s, g.pad, g.ho,
+                            g.wo, magic_of((uint32_t)g.wo),                       magic_of((uint32_t)g.ho),   N,   K};
   Epilogue ep{};
   ep.alpha = 1.0f;
   ep.D = dw;
@@ -186,8 +215,16 @@ mdnn_status_t filter_run(const ConvGeom& g, const void* x, const void* dy, float
     ep.partial = (float*)ws;
     ep.k_per_split = p.k_per_split;
   }
-  MDNN_TRY((run_pipe<T, F32, TL, FILTER_STAGES, lds::MatLoader<false, TL::BM, TL::LA>,
-                     lds::ConvColsLoader<TL::BN, TL::LB>>(a, b, M, N, K, ep, p.splits, st)));
+  // a size-preserving layer over whole K steps keeps the plain dy loader and
+  // the shorter column arithmetic
+  if (g.ho == g.h && g.wo == g.w && K % lds::BK == 0)
+    MDNN_TRY((run_pipe<T, F32, TL, FILTER_STAGES, lds::MatLoader<false, TL::BM, TL::LA>,
+                       lds::ConvColsLoader<TL::BN, TL::LB, true>>(lds::MatArgs{dy, g.k, g.k}, b, M, N, K, ep, p.splits,
+                                                                  st)));
+  else
+    MDNN_TRY((run_pipe<T, F32, TL, FILTER_STAGES, lds::MatLoaderRC<false, TL::BM, TL::LA>,
+                       lds::ConvColsLoader<TL::BN, TL::LB, false>>(
+        lds::MatRCArgs{dy, (uint32_t)(K * g.k * 2), g.k, g.k, K}, b, M, N, K, ep, p.splits, st)));
   if (p.splits > 1) return reduce_splits((const float*)ws, p.splits, M, N, dw, st, defer);
   return MDNN_SUCCESS;
 }

@@ -16,10 +16,11 @@
 //   ConvRowsLoader   im2col rows of a convolution input (forward: x, backward
 //                    data: dy with mirrored taps); one K step is 64 channels of
 //                    one filter tap, so the tap shift is uniform per step.
-//   ConvRows32Loader forward im2col rows when c_in is a multiple of 32 only:
-//                    a K step is 32 channels of two taps (per-lane tap state),
-//                    with MatLoaderRC reading the filter range-checked.
-//   TapWeightLoader  the filter read as [tap, c_out] x [c_in] (backward data).
+//   ConvRuns8Loader  im2col rows for channel counts that are multiples of 8:
+//                    k walks runs of one filter row's elements.
+//   MatLoaderRC      plain matrix whose K is no multiple of the step.
+//   TapWeightLoader, TapRowsLoader  the filter read as [tap, c_out] x [c_in]
+//                    (backward data; c_out % 64 == 0, any c_out).
 //   ConvColsLoader   shifted input columns of the backward-filter GEMM
 //                    (K = output pixels, N = (tap, c_in)).
 // The convolution loaders use buffer_load ... lds with a range-checked buffer
@@ -42,7 +43,8 @@
 //     consecutive k.  Each half-wave then touches 8 distinct 32-byte bank
 //     groups.
 //
-// Preconditions (checked by the host): K % 64 == 0 (per split); 16-byte
+// Preconditions (checked by the host): K % 64 == 0 (per split; any K with the
+// range-checked loaders, which read zeros past it); 16-byte
 // aligned bases; plain operands: leading dimensions multiple of 8, an
 // MN-contiguous operand's MN a multiple of 8 and >= 8, per-lane byte offsets
 // within one K step below 2^32; convolution loaders: channel counts as the
@@ -209,7 +211,6 @@ struct ConvRowsArgs {
   int32_t ho, wo;     // GEMM row grid
   int32_t s, pad, flip;
   int64_t M;
-  int32_t r;          // filter rows (ConvRows32Loader only)
 };
 template <int W, int L>
 struct ConvRowsLoader {
@@ -265,113 +266,124 @@ struct ConvRowsLoader {
   }
 };
 
-// im2col rows for a forward convolution whose input channel count is a
-// multiple of 32 but not of 64: a K step is two 32-channel half blocks,
-// half block h = tap * (c / 32) + b holding channels 32b .. 32b + 31 of one
-// tap, so GEMM column kk = tap * c + ch as in the filter's own layout.  The
-// K range is padded to whole steps: a half block past the last tap reads
-// zeros (its filter columns are then multiplied by zero).
+// im2col rows for any channel count that is a multiple of 8: for one filter
+// row the s * c elements under an output pixel are one run of the image row,
+// and k walks run by run, so GEMM column kk = r * (s * c) + e as in the
+// filter's own layout.  A 16-byte chunk lies in one tap, so it is read whole
+// or (left, right, above, below the image, or past the last filter row: K
+// padded to whole steps) as zeros.  Backward data reads dy the same way with
+// the mirrored filter (pad' = r - 1 - pad).
+struct ConvRunsArgs {
+  const void* p;
+  uint32_t bytes;
+  int32_t hs, wsC, c;  // source rows, elements per source row, channels
+  int32_t ho, wo;      // GEMM row grid
+  int32_t r, len;      // filter rows, s * c
+  uint32_t magic;      // ceil(2^32 / len)
+  int32_t padr, pads;  // rows above, pixels left
+  int64_t M;
+};
 template <int W, int L>
-struct ConvRows32Loader {
+struct ConvRuns8Loader {
   static constexpr bool KC = true;
-  static constexpr bool SPLIT_ISSUE = false;  // the per-step state advances once per tile
-  typedef ConvRowsArgs Args;
+  static constexpr bool SPLIT_ISSUE = false;
+  typedef ConvRunsArgs Args;
   // A lane's k offset within a step (load_pos) depends on its load index
-  // only through the index's parity when L is even (block wave * L + i), so
-  // the tap state is kept for P = 2 loads, not L.
-  static_assert(L == 1 || L % 2 == 0, "tap state per load parity");
+  // only through the index's parity when L is even (block wave * L + i).
+  static_assert(L == 1 || L % 2 == 0, "k offset per load parity");
   static constexpr int P = L >= 2 ? 2 : 1;
   int4_t rsrc;
-  int32_t hs, ws, c, s, r, pad, cpb;
-  uint32_t base[L];
-  int32_t ii[L], jj[L];
-  int32_t tr[P], ts[P], chb[P], ch[P];
+  int32_t hs, wsC, rows, len;
+  uint32_t magic, k0;
+  uint32_t base[L];  // bytes
+  int32_t iy[L], jc[L], kc[P];
 
-  __device__ __forceinline__ void init(const ConvRowsArgs& a, int64_t mn0, int64_t kbeg, int wave, int lane) {
+  __device__ __forceinline__ void init(const ConvRunsArgs& a, int64_t mn0, int64_t kbeg, int wave, int lane) {
     rsrc = make_rsrc(a.p, a.bytes);
-    hs = a.hs, ws = a.ws, c = a.c, s = a.s, r = a.r, pad = a.pad;
-    cpb = a.c / 32;
-    const int32_t kt = (int32_t)(kbeg / BK);
+    hs = a.hs, wsC = a.wsC, rows = a.r, len = a.len, magic = a.magic, k0 = (uint32_t)kbeg;
     const int32_t hw = a.ho * a.wo;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const LoadPos q = load_pos<true, W, L>(wave, lane, i);
-      if (i < P) {
-        const int32_t h = 2 * kt + q.c / 32, tap = h / cpb;
-        chb[i] = h - tap * cpb;
-        tr[i] = tap / a.s;
-        ts[i] = tap - tr[i] * a.s;
-        ch[i] = q.c % 32;
-      }
+      if (i < P) kc[i] = q.c;
       const int64_t m = mn0 + q.r;
       if (m < a.M) {
         const int32_t mi = (int32_t)m, n = mi / hw, rem = mi - n * hw, i0 = rem / a.wo, j0 = rem - i0 * a.wo;
-        ii[i] = i0;
-        jj[i] = j0;
-        base[i] = (uint32_t)(((n * a.hs + i0) * a.ws + j0) * a.c * 2);
+        iy[i] = i0 - a.padr;
+        jc[i] = (j0 - a.pads) * a.c;
+        base[i] = (uint32_t)((n * a.hs + iy[i]) * a.wsC + jc[i]) * 2u;
       } else {
-        ii[i] = -(1 << 20);  // outside the grid for every tap
-        jj[i] = 0;
+        iy[i] = -(1 << 20);  // outside the image for every filter row
+        jc[i] = 0;
         base[i] = 0;
       }
     }
   }
-  __device__ __forceinline__ void issue(int, uint32_t dst) {
+  __device__ __forceinline__ void issue(int t, uint32_t dst) {
+    int32_t r[P], e[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const uint32_t k = k0 + (uint32_t)t * BK + (uint32_t)kc[q];
+      r[q] = (int32_t)fast_div(k, magic);
+      e[q] = (int32_t)k - r[q] * len;
+      if (r[q] >= rows) e[q] = -(1 << 30);  // past the filter: outside every image row
+    }
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const int p = i % P;
-      const int32_t dh = tr[p] - pad, dw = ts[p] - pad;
-      const bool ok = tr[p] < r && (uint32_t)(ii[i] + dh) < (uint32_t)hs && (uint32_t)(jj[i] + dw) < (uint32_t)ws;
-      const uint32_t off = base[i] + (uint32_t)(((dh * ws + dw) * c + chb[p] * 32 + ch[p]) * 2);
-      dma_buffer(rsrc, ok ? off : OOB, dst + (uint32_t)i * 1024u);
-    }
-    // two half blocks on: at most two tap advances (cpb >= 1)
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      chb[p] += 2;
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        if (chb[p] >= cpb) {
-          chb[p] -= cpb;
-          if (++ts[p] == s) {
-            ts[p] = 0;
-            ++tr[p];
-          }
-        }
-      }
+      const bool ok = (uint32_t)(iy[i] + r[p]) < (uint32_t)hs && (uint32_t)(jc[i] + e[p]) < (uint32_t)wsC;
+      dma_buffer(rsrc, ok ? base[i] + (uint32_t)((r[p] * wsC + e[p]) * 2) : OOB, dst + (uint32_t)i * 1024u);
     }
   }
 };
 
-// A K-contiguous matrix [MN][ld] read through a range-checked buffer
-// resource: columns past the end of the last row (a K range padded to whole
-// steps) read as zero instead of past the allocation.
+// A plain matrix read through a range-checked buffer resource, for a K that
+// is not a multiple of the step: k past K reads as zero (in the K-contiguous
+// order by the test below, K a multiple of 8; k-rows of the MN-contiguous
+// order lie past the buffer, whose size ends with row K - 1).
 struct MatRCArgs {
   const void* p;
   uint32_t bytes;
-  int64_t ld, MN;
+  int64_t ld, MN, K;
 };
-template <int W, int L>
+template <bool KC_, int W, int L>
 struct MatLoaderRC {
-  static constexpr bool KC = true;
+  static constexpr bool KC = KC_;
   static constexpr bool SPLIT_ISSUE = false;
+  static constexpr int P = KC && L >= 2 ? 2 : 1;
   typedef MatRCArgs Args;
   int4_t rsrc;
+  uint32_t step;
+  int32_t left[P];  // K-contiguous: k from this lane's chunk to the end
   uint32_t off[L];
 
   __device__ __forceinline__ void init(const MatRCArgs& a, int64_t mn0, int64_t kbeg, int wave, int lane) {
     rsrc = make_rsrc(a.p, a.bytes);
+    step = (uint32_t)(KC ? BK * 2 : BK * a.ld * 2);
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const LoadPos q = load_pos<true, W, L>(wave, lane, i);
-      int64_t row = mn0 + q.r;
-      if (row >= a.MN) row = a.MN - 1;
-      off[i] = (uint32_t)((row * a.ld + kbeg + q.c) * 2);
+      const LoadPos q = load_pos<KC, W, L>(wave, lane, i);
+      if constexpr (KC) {
+        int64_t row = mn0 + q.r;
+        if (row >= a.MN) row = a.MN - 1;
+        if (i < P) left[i] = (int32_t)(a.K - kbeg - q.c);
+        off[i] = (uint32_t)((row * a.ld + kbeg + q.c) * 2);
+      } else {
+        int64_t mn = mn0 + q.c;
+        if (mn + 8 > a.MN) mn = a.MN - 8;
+        off[i] = (uint32_t)(((kbeg + q.r) * a.ld + mn) * 2);
+      }
     }
   }
   __device__ __forceinline__ void issue(int t, uint32_t dst) {
 #pragma unroll
-    for (int i = 0; i < L; ++i) dma_buffer(rsrc, off[i] + (uint32_t)t * (BK * 2), dst + (uint32_t)i * 1024u);
+    for (int i = 0; i < L; ++i) {
+      const uint32_t o = off[i] + (uint32_t)t * step;
+      if constexpr (KC)
+        dma_buffer(rsrc, t * BK < left[i % P] ? o : OOB, dst + (uint32_t)i * 1024u);
+      else
+        dma_buffer(rsrc, o, dst + (uint32_t)i * 1024u);
+    }
   }
 };
 
@@ -420,34 +432,77 @@ struct TapWeightLoader {
   }
 };
 
-// Shifted input columns of the backward-filter GEMM for a size-preserving
-// convolution (ho == h, wo == w): k-row = output pixel p = (n, i, j), column
-// nn = tap * c + ch -> x[n, i + tr - pad, j + ts - pad, ch] (zero outside),
-// which is x's element p * c + ((tr - pad) * w + ts - pad) * c + ch.
-// Requires c % 8 == 0.
+// The same for any c_out (a K step may span taps): k = mirrored tap * c_out +
+// filter, each lane's k-row found per step.  Requires c_in % 8 == 0.
+struct TapRowsArgs {
+  const void* p;
+  uint32_t bytes;
+  int32_t c_out, taps, c_in;
+  uint32_t magic;  // ceil(2^32 / c_out), 0 for 1
+};
+template <int W, int L>
+struct TapRowsLoader {
+  static constexpr bool KC = false;
+  static constexpr bool SPLIT_ISSUE = false;
+  typedef TapRowsArgs Args;
+  int4_t rsrc;
+  int32_t nf, taps, c_in;
+  uint32_t magic, k0;
+  int32_t krow[L], col[L];
+
+  __device__ __forceinline__ void init(const TapRowsArgs& a, int64_t mn0, int64_t kbeg, int wave, int lane) {
+    rsrc = make_rsrc(a.p, a.bytes);
+    nf = a.c_out, taps = a.taps, c_in = a.c_in, magic = a.magic, k0 = (uint32_t)kbeg;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const LoadPos q = load_pos<false, W, L>(wave, lane, i);
+      krow[i] = q.r;
+      col[i] = mn0 + q.c < a.c_in ? (int32_t)mn0 + q.c : 0;
+    }
+  }
+  __device__ __forceinline__ void issue(int t, uint32_t dst) {
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const uint32_t k = k0 + (uint32_t)t * BK + (uint32_t)krow[i];
+      const int32_t tap = (int32_t)fast_div(k, magic), f = (int32_t)k - tap * nf;
+      const uint32_t off = (uint32_t)((f * taps + taps - 1 - tap) * c_in + col[i]) * 2u;
+      dma_buffer(rsrc, tap < taps ? off : OOB, dst + (uint32_t)i * 1024u);
+    }
+  }
+};
+
+// Shifted input columns of the backward-filter GEMM: k-row = output pixel
+// p = (n, i, j), column nn = tap * c + ch -> x[n, i + tr - pad, j + ts - pad,
+// ch] (zero outside, and past the last pixel).  For a size-preserving
+// convolution (SAME: ho == h, wo == w) that is x's element
+// p * c + ((tr - pad) * w + ts - pad) * c + ch; otherwise rows and images are
+// further apart in x than in the pixel index.  Requires c % 8 == 0.
 struct ConvColsArgs {
   const void* p;
   uint32_t bytes;
-  int32_t h, w, c, s, pad;
-  uint32_t magic_w, magic_h;  // ceil(2^32 / w), ceil(2^32 / h); 0 for 1
-  int64_t N;
+  int32_t h, w, c, s, pad, ho, wo;
+  uint32_t magic_w, magic_h;  // ceil(2^32 / wo), ceil(2^32 / ho); 0 for 1
+  int64_t N, K;
 };
-template <int W, int L>
+template <int W, int L, bool SAME>
 struct ConvColsLoader {
   static constexpr bool KC = false;
   static constexpr bool SPLIT_ISSUE = false;  // the per-step state advances once per tile
   typedef ConvColsArgs Args;
   int4_t rsrc;
-  int32_t h, w;
-  uint32_t magic_w, magic_h, row_bytes, pix0;
+  int32_t h, w, ho, wo;
+  uint32_t magic_w, magic_h, row_bytes, pix0, npix, row_gap, img_gap;
   int32_t dh[L], dw[L], coff[L], krow[L];
 
   __device__ __forceinline__ void init(const ConvColsArgs& a, int64_t mn0, int64_t kbeg, int wave, int lane) {
     rsrc = make_rsrc(a.p, a.bytes);
-    h = a.h, w = a.w;
+    h = a.h, w = a.w, ho = a.ho, wo = a.wo;
     magic_w = a.magic_w, magic_h = a.magic_h;
     row_bytes = (uint32_t)a.c * 2u;
+    row_gap = (uint32_t)(a.w - a.wo) * row_bytes;
+    img_gap = (uint32_t)((a.h - a.ho) * a.w) * row_bytes;
     pix0 = (uint32_t)kbeg;
+    npix = (uint32_t)a.K;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const LoadPos q = load_pos<false, W, L>(wave, lane, i);
@@ -472,11 +527,13 @@ struct ConvColsLoader {
     for (int i = 0; i < L; ++i) {
       const uint32_t px = p0 + (uint32_t)krow[i];
       const uint32_t q1 = fast_div(px, magic_w);
-      const int32_t j = (int32_t)(px - q1 * (uint32_t)w);
+      const int32_t j = (int32_t)(px - q1 * (uint32_t)wo);
       const uint32_t q2 = fast_div(q1, magic_h);
-      const int32_t ii = (int32_t)(q1 - q2 * (uint32_t)h);
-      const bool ok = (uint32_t)(ii + dh[i]) < (uint32_t)h && (uint32_t)(j + dw[i]) < (uint32_t)w;
-      dma_buffer(rsrc, ok ? px * row_bytes + (uint32_t)coff[i] : OOB, dst + (uint32_t)i * 1024u);
+      const int32_t ii = (int32_t)(q1 - q2 * (uint32_t)ho);
+      const bool ok = px < npix && (uint32_t)(ii + dh[i]) < (uint32_t)h && (uint32_t)(j + dw[i]) < (uint32_t)w;
+      uint32_t off = px * row_bytes + (uint32_t)coff[i];
+      if constexpr (!SAME) off += q1 * row_gap + q2 * img_gap;
+      dma_buffer(rsrc, ok ? off : OOB, dst + (uint32_t)i * 1024u);
     }
   }
 };
@@ -879,7 +936,7 @@ gemm_lds_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
     kbeg = (int64_t)split * ep.k_per_split;
     kend = kbeg + ep.k_per_split < K ? kbeg + ep.k_per_split : K;
   }
-  const int nk = (int)((kend - kbeg) / BK);
+  const int nk = (int)ceil_div(kend - kbeg, (int64_t)BK);  // (a ragged last step: the loaders read zeros past K)
 
   LA la;
   LB lb;

@@ -1,8 +1,8 @@
-"""Convolutions on the register-staged kernel: fp32 data and channel counts
-that are no multiple of 8, at the edges of its runs (one filter row of
-s * c elements, padded to 8 16-bit or 4 fp32 ones), tiles and K steps, all
-three passes against the oracle; NaN around every operand must not reach a
-result."""
+"""Convolutions of any channel count: on the register-staged kernel (fp32 data
+and channel counts that are no multiple of 8) at the edges of its runs (one
+filter row of s * c elements, padded to 8 16-bit or 4 fp32 ones), tiles and K
+steps, and on the direct-to-LDS kernel for multiples of 8; all three passes
+against the oracle; NaN around every operand must not reach a result."""
 import numpy as np
 import pytest
 
@@ -36,6 +36,29 @@ SHAPES = [
 @pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_conv_any_channels(mdnn, shape, dt):
+    _check(mdnn, shape, dt, 1)
+
+
+# Channel counts that are multiples of 8 but not of 64, on the direct-to-LDS
+# kernel: one chunk per tap, a K step over several taps and filter rows, K and
+# pixel counts that end inside a step, valid and over-wide padding (filter
+# gradients whose output grid is not the input's), outputs that take the 256 x
+# 64 tile past 128 columns (200) and the 64 x 128 one, one-pixel-wide images.
+SHAPES8 = [
+    (2, 9, 7, 8, 16, 3, 3, 1), (3, 8, 8, 24, 40, 5, 5, 2), (2, 7, 9, 72, 88, 3, 3, 0), (1, 6, 5, 16, 8, 3, 3, 2),
+    (4, 13, 1, 40, 136, 3, 3, 1), (2, 10, 11, 48, 200, 1, 1, 0), (9, 11, 13, 96, 80, 5, 5, 2), (2, 5, 6, 104, 72, 2, 4, 3),
+    (3, 90, 91, 8, 200, 3, 3, 1), (5, 12, 13, 64, 64, 3, 3, 0), (2, 6, 6, 8, 8, 7, 7, 3),
+]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES8)
+def test_conv_multiples_of_8_channels(mdnn, shape, dt):
+    _check(mdnn, shape, dt, 8)
+
+
+def _check(mdnn, shape, dt, gap):
+    """All three passes, each operand `gap` elements into a buffer of NaN."""
     import torch
     n, h, w, ci, co, r, s, pad = shape
     ho, wo = h + 2 * pad - r + 1, w + 2 * pad - s + 1
@@ -44,10 +67,10 @@ def test_conv_any_channels(mdnn, shape, dt):
     val = {k: decode(v, dt) for k, v in arr.items()}
     mag = {k: np.abs(v) for k, v in val.items()}
     buf, t = {}, {}
-    for k, v in arr.items():     # each operand one element into a buffer of NaN
+    for k, v in arr.items():
         d = dev(v, dt).reshape(-1)
-        buf[k] = torch.full((d.numel() + 2,), float("nan"), dtype=d.dtype, device="cuda")
-        t[k] = buf[k][1:-1]
+        buf[k] = torch.full((d.numel() + 2 * gap,), float("nan"), dtype=d.dtype, device="cuda")
+        t[k] = buf[k][gap:-gap]
         t[k].copy_(d)
     sh = mdnn.ConvShape(n, h, w, ci, co, r, s, pad)
     y = torch.full((n, ho, wo, co), float("nan"), device="cuda")
