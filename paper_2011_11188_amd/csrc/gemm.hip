@@ -142,8 +142,10 @@ mdnn_status_t reduce_splits(const float* partial, int splits, int64_t rows, int6
 //
 // With a workspace (two passes): pass 1 splits the rows into chunks of
 // COLSUM_ROWS; a block reduces one chunk x 64 columns (8 column groups of 8
-// read as 16-byte vectors, 32 row lanes, then a fixed-order combine in LDS)
-// into partial[chunk][col].  Pass 2 sums the partials of each column with
+// read as 16-byte vectors at any element address, 32 row lanes, then a
+// fixed-order combine in LDS) into partial[chunk][col].  HBM-bound when tall
+// (262144 x 64 fp32 35.9 -> 15.2 us, 4.4 TB/s), else by its loads' latency:
+// with element loads for fp32 and odd widths 1000 x 777 fp16 took 11.6 us, 5.0 now.  Pass 2 sums the partials of each column with
 // the split reduction below (many chunks) or 8 strided lanes per column (few
 // chunks), each combined in a fixed order.
 // Without a workspace: one block per 32 columns walks all rows (slow for very
@@ -156,57 +158,146 @@ __device__ __forceinline__ float masked_val(const typename T::storage* x, const 
   return (y == nullptr || to_f<T>(y[i]) > 0.0f) ? to_f<T>(x[i]) : 0.0f;
 }
 
+// Eight consecutive elements of a row at any element address.
 template <class T>
+struct Row8 {
+  uint4 q[sizeof(typename T::storage) / 2];
+  __device__ __forceinline__ void load(const typename T::storage* p) {
+    typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+    typedef v4 v4a2 __attribute__((aligned(2)));
+    typedef v4 v4a4 __attribute__((aligned(4)));
+#pragma unroll
+    for (int h = 0; h < (int)sizeof(typename T::storage) / 2; ++h) {
+      v4 t;
+      if constexpr (sizeof(typename T::storage) == 2)
+        t = *(const __attribute__((address_space(1))) v4a2*)p;
+      else
+        t = *(const __attribute__((address_space(1))) v4a4*)(p + 4 * h);
+      q[h] = make_uint4(t.x, t.y, t.z, t.w);
+    }
+  }
+  __device__ __forceinline__ float get(int e) const {
+    if constexpr (sizeof(typename T::storage) == 2) {
+      const uint32_t w = e / 2 == 0 ? q[0].x : e / 2 == 1 ? q[0].y : e / 2 == 2 ? q[0].z : q[0].w;
+      return to_f<T>((uint16_t)(w >> ((e & 1) * 16)));
+    } else {
+      const uint4& v = q[sizeof(typename T::storage) == 4 ? e / 4 : 0];
+      const uint32_t w = e % 4 == 0 ? v.x : e % 4 == 1 ? v.y : e % 4 == 2 ? v.z : v.w;
+      return __builtin_bit_cast(float, w);
+    }
+  }
+};
+
+// Sums of 8 columns from c0 on over rows r0, r0 + step, ... < r1, added in
+// row order, U rows' loads in flight (any alignment; the caller keeps c0 + 8
+// <= cols, so every load lies in its row).
+template <class T, int U, bool MASK>
+__device__ __forceinline__ void sum_rows8(const typename T::storage* __restrict__ x,
+                                          const typename T::storage* __restrict__ y, int64_t r0, int64_t r1, int step,
+                                          int64_t cols, int64_t c0, float (&s)[8]) {
+  for (int64_t r = r0; r < r1; r += (int64_t)U * step) {
+    Row8<T> v[U], m[MASK ? U : 1];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t row = r + (int64_t)u * step < r1 ? r + (int64_t)u * step : r1 - 1;
+      v[u].load(x + row * cols + c0);
+      if constexpr (MASK) m[u].load(y + row * cols + c0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (r + (int64_t)u * step < r1) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (!MASK || m[MASK ? u : 0].get(e) > 0.0f) s[e] += v[u].get(e);
+      }
+  }
+}
+
+// A block's 8 columns per thread: group cg of `groups` covers columns
+// from .. from + 7; the last group of a row starts early enough to lie in the
+// row and leaves out the columns its neighbour has (`first` of the eight).
+struct ColGroup {
+  int64_t from;
+  int first, n;  // columns first .. n - 1 of the eight are this thread's
+};
+__device__ __forceinline__ ColGroup col_group(int64_t c0, int64_t cols) {
+  if (c0 >= cols) return {0, 0, 0};
+  if (c0 + 8 <= cols) return {c0, 0, 8};
+  return {cols - 8, (int)(c0 - (cols - 8)), 8};
+}
+
+template <class T, bool MASK>
 __global__ void __launch_bounds__(256)
 colsum_partial_kernel(const typename T::storage* __restrict__ x, const typename T::storage* __restrict__ y,
-                      int64_t rows, int64_t cols, bool vec, float* __restrict__ partial) {
+                      int64_t rows, int64_t cols, float* __restrict__ partial) {
   __shared__ float red[32][65];
   const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
   const int64_t c0 = (int64_t)blockIdx.x * 64 + cg * 8;
   const int64_t r0 = (int64_t)blockIdx.y * COLSUM_ROWS;
   const int64_t r1 = r0 + COLSUM_ROWS < rows ? r0 + COLSUM_ROWS : rows;
   float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // adds one row's 8 values (16 bytes of x, and of the mask y) to s
-  auto add8 = [&](const uint4& v, const uint4& m) {
-    const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-    const uint32_t mw[4] = {m.x, m.y, m.z, m.w};
+  if (cols >= 8) {
+    const ColGroup g = col_group(c0, cols);
+    // a whole chunk's rows of this thread (8) in flight, fp32 in two halves
+    if (g.n) sum_rows8<T, sizeof(typename T::storage) == 2 ? 8 : 4, MASK>(x, y, r0 + rl, r1, 32, cols, g.from, s);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint16_t xv = (uint16_t)(vw[e >> 1] >> ((e & 1) * 16));
-      const uint16_t yv = (uint16_t)(mw[e >> 1] >> ((e & 1) * 16));
-      if (y == nullptr || to_f<T>((typename T::storage)yv) > 0.0f) s[e] += to_f<T>((typename T::storage)xv);
-    }
-  };
-  const uint4 ones = make_uint4(0xffffffffu, 0xffffffffu, 0xffffffffu, 0xffffffffu);
-  if (vec && sizeof(typename T::storage) == 2 && c0 + 8 <= cols && r1 - r0 == COLSUM_ROWS) {
-    // a whole chunk: all of this thread's rows are loaded before any is added
-    // (same order of additions as the row loop below)
-    constexpr int RPT = COLSUM_ROWS / 32;
-    uint4 v[RPT], m[RPT];
-#pragma unroll
-    for (int u = 0; u < RPT; ++u) v[u] = *(const uint4*)(x + (r0 + rl + 32 * u) * cols + c0);
-#pragma unroll
-    for (int u = 0; u < RPT; ++u) m[u] = y ? *(const uint4*)(y + (r0 + rl + 32 * u) * cols + c0) : ones;
-#pragma unroll
-    for (int u = 0; u < RPT; ++u) add8(v[u], m[u]);
-  } else if (vec && sizeof(typename T::storage) == 2 && c0 + 8 <= cols) {
-    for (int64_t r = r0 + rl; r < r1; r += 32)
-      add8(*(const uint4*)(x + r * cols + c0), y ? *(const uint4*)(y + r * cols + c0) : ones);
+    for (int e = 0; e < 8; ++e)
+      if (e >= g.first && e < g.n) red[rl][cg * 8 + e - g.first] = s[e];
   } else {
     for (int64_t r = r0 + rl; r < r1; r += 32)
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (c0 + e < cols) s[e] += masked_val<T>(x, y, r * cols + c0 + e);
-  }
+        if (c0 + e < cols) s[e] += masked_val<T>(x, MASK ? y : nullptr, r * cols + c0 + e);
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[rl][cg * 8 + e] = s[e];
+    for (int e = 0; e < 8; ++e) red[rl][cg * 8 + e] = s[e];
+  }
   __syncthreads();
   if (threadIdx.x < 64) {
     const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (c >= cols) return;
     float t = red[0][threadIdx.x];
     for (int k = 1; k < 32; ++k) t += red[k][threadIdx.x];
-    if (c < cols) partial[(int64_t)blockIdx.y * cols + c] = t;
+    partial[(int64_t)blockIdx.y * cols + c] = t;
   }
+}
+
+// Up to COLSUM_ONCE_ROWS rows in one launch: a block of 1024 threads walks
+// all rows of 64 columns (8 column groups x 128 row lanes, eight rows of a
+// thread in flight), then combines the lanes by a fixed tree.  The two-pass
+// form pays a second launch for the same bytes but spreads tall columns over
+// more blocks: at 4096 x 1000 fp32 it takes half the time (1024 x 2048 fp32
+// in one launch 4.5 us, 4097 x 64 in two 5.2 us).
+constexpr int64_t COLSUM_ONCE_ROWS = 1024;
+template <class T, bool MASK>
+__global__ void __launch_bounds__(1024)
+colsum_once_kernel(const typename T::storage* __restrict__ x, const typename T::storage* __restrict__ y,
+                   int64_t rows, int64_t cols, float* __restrict__ out) {
+  __shared__ float red[128][65];
+  const int cg = threadIdx.x & 7, rl = threadIdx.x >> 3;
+  const ColGroup g = col_group((int64_t)blockIdx.x * 64 + cg * 8, cols);
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (g.n) sum_rows8<T, sizeof(typename T::storage) == 2 ? 8 : 4, MASK>(x, y, rl, rows, 128, cols, g.from, s);
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (e >= g.first && e < g.n) red[rl][cg * 8 + e - g.first] = s[e];
+  __syncthreads();
+  // thread t: column t % 64, lanes 8 (t / 64) .. + 7 in order; then a tree over the 16 sums
+  const int c = threadIdx.x & 63, h = threadIdx.x >> 6;
+  const bool in = (int64_t)blockIdx.x * 64 + c < cols;
+  float t = 0.0f;
+  if (in) {
+    t = red[8 * h][c];
+#pragma unroll
+    for (int k = 1; k < 8; ++k) t += red[8 * h + k][c];
+  }
+  __syncthreads();
+  if (in) red[h][c] = t;
+  __syncthreads();
+  for (int k = 8; k > 0; k >>= 1) {
+    if (h < k && in) red[h][c] += red[h + k][c];
+    __syncthreads();
+  }
+  if (h == 0 && in) out[(int64_t)blockIdx.x * 64 + c] = red[0][c];
 }
 
 // Pass 1 of the split API for 16-bit rows whose width is a multiple of 512
@@ -371,29 +462,31 @@ size_t column_sums_ws_bytes(int64_t rows, int64_t cols) {
   return (size_t)ceil_div(rows, COLSUM_ROWS) * (size_t)cols * sizeof(float);
 }
 
-template <class T>
-static mdnn_status_t colsum_launch(const void* x, const void* y, int64_t rows, int64_t cols, float* out,
+template <class T, bool MASK>
+static mdnn_status_t colsum_launch(const void* xv, const void* yv, int64_t rows, int64_t cols, float* out,
                                    void* ws, size_t ws_bytes, hipStream_t st, ReduceBatch* defer) {
   typedef typename T::storage S;
+  const S* x = (const S*)xv;
+  const S* y = (const S*)yv;
   const size_t need = column_sums_ws_bytes(rows, cols);
-  const bool vec = aligned(x, 16) && (!y || aligned(y, 16)) && cols % 8 == 0;
-  if (rows <= COLSUM_ROWS) {
-    // one chunk: pass 1 alone gives the sums (its 16-byte row reads keep
-    // more loads in flight than the single-pass kernel)
-    hipLaunchKernelGGL(colsum_partial_kernel<T>, dim3((unsigned)ceil_div(cols, 64), 1u), dim3(256), 0, st,
-                       (const S*)x, (const S*)y, rows, cols, vec, out);
+  const unsigned bx = (unsigned)ceil_div(cols, 64);
+  if (rows <= COLSUM_ONCE_ROWS && rows > 0 && cols >= 8) {
+    hipLaunchKernelGGL((colsum_once_kernel<T, MASK>), dim3(bx), dim3(1024), 0, st, x, y, rows, cols, out);
+  } else if (rows <= COLSUM_ROWS) {
+    // one chunk: pass 1 alone gives the sums
+    hipLaunchKernelGGL((colsum_partial_kernel<T, MASK>), dim3(bx, 1u), dim3(256), 0, st, x, y, rows, cols, out);
   } else if (need > 0 && ws && ws_bytes >= need && aligned(ws, 4)) {
     const int64_t chunks = ceil_div(rows, COLSUM_ROWS);
-    hipLaunchKernelGGL(colsum_partial_kernel<T>, dim3((unsigned)ceil_div(cols, 64), (unsigned)chunks), dim3(256),
-                       0, st, (const S*)x, (const S*)y, rows, cols, vec, (float*)ws);
+    hipLaunchKernelGGL((colsum_partial_kernel<T, MASK>), dim3(bx, (unsigned)chunks), dim3(256), 0, st, x, y, rows,
+                       cols, (float*)ws);
     MDNN_TRY(check_launch("column sums (partials)"));
     if (chunks >= 32 && cols <= ((int64_t)1 << 18))
       return reduce_wide((const float*)ws, (int)chunks, cols, out, st, defer);
     hipLaunchKernelGGL(colsum_final_kernel, dim3((unsigned)ceil_div(cols, 32)), dim3(256), 0, st,
                        (const float*)ws, chunks, cols, out);
   } else {
-    hipLaunchKernelGGL(colsum_single_kernel<T>, dim3((unsigned)ceil_div(cols, 32)), dim3(256), 0, st,
-                       (const S*)x, (const S*)y, rows, cols, out);
+    hipLaunchKernelGGL(colsum_single_kernel<T>, dim3((unsigned)ceil_div(cols, 32)), dim3(256), 0, st, x, y, rows, cols,
+                       out);
   }
   return check_launch("column sums");
 }
@@ -403,9 +496,15 @@ mdnn_status_t column_sums(const void* x, const void* y, mdnn_dtype_t t, int64_t 
   if (cols == 0) return MDNN_SUCCESS;
   if (ceil_div(rows, COLSUM_ROWS) > 65535) ws = nullptr;  // grid limit: single pass
   switch (t) {
-    case MDNN_F32: return colsum_launch<F32>(x, y, rows, cols, out, ws, ws_bytes, stream, defer);
-    case MDNN_F16: return colsum_launch<F16>(x, y, rows, cols, out, ws, ws_bytes, stream, defer);
-    default: return colsum_launch<BF16>(x, y, rows, cols, out, ws, ws_bytes, stream, defer);
+    case MDNN_F32:
+      return y ? colsum_launch<F32, true>(x, y, rows, cols, out, ws, ws_bytes, stream, defer)
+               : colsum_launch<F32, false>(x, y, rows, cols, out, ws, ws_bytes, stream, defer);
+    case MDNN_F16:
+      return y ? colsum_launch<F16, true>(x, y, rows, cols, out, ws, ws_bytes, stream, defer)
+               : colsum_launch<F16, false>(x, y, rows, cols, out, ws, ws_bytes, stream, defer);
+    default:
+      return y ? colsum_launch<BF16, true>(x, y, rows, cols, out, ws, ws_bytes, stream, defer)
+               : colsum_launch<BF16, false>(x, y, rows, cols, out, ws, ws_bytes, stream, defer);
   }
 }
 
@@ -429,19 +528,18 @@ mdnn_status_t column_sums_partial(const void* x, mdnn_dtype_t t, int64_t rows, i
     return check_launch("column sums (partials)");
   }
   const dim3 grid((unsigned)ceil_div(cols, 64), (unsigned)chunks);
-  const bool vec = aligned(x, 16) && cols % 8 == 0;
   switch (t) {
     case MDNN_F32:
-      hipLaunchKernelGGL(colsum_partial_kernel<F32>, grid, dim3(256), 0, st, (const float*)x, nullptr, rows, cols,
-                         vec, partial);
+      hipLaunchKernelGGL((colsum_partial_kernel<F32, false>), grid, dim3(256), 0, st, (const float*)x, nullptr, rows,
+                         cols, partial);
       break;
     case MDNN_F16:
-      hipLaunchKernelGGL(colsum_partial_kernel<F16>, grid, dim3(256), 0, st, (const uint16_t*)x, nullptr, rows,
-                         cols, vec, partial);
+      hipLaunchKernelGGL((colsum_partial_kernel<F16, false>), grid, dim3(256), 0, st, (const uint16_t*)x, nullptr,
+                         rows, cols, partial);
       break;
     default:
-      hipLaunchKernelGGL(colsum_partial_kernel<BF16>, grid, dim3(256), 0, st, (const uint16_t*)x, nullptr, rows,
-                         cols, vec, partial);
+      hipLaunchKernelGGL((colsum_partial_kernel<BF16, false>), grid, dim3(256), 0, st, (const uint16_t*)x, nullptr,
+                         rows, cols, partial);
   }
   return check_launch("column sums (partials)");
 }

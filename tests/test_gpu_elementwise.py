@@ -10,7 +10,7 @@ import pytest
 import workloads as W
 from oracle import ops
 from oracle.rounding import decode, round_to
-from tests.helpers import DT, dev, empty, host64, lowp_close, norm_max_err
+from tests.helpers import DT, accum_bound, dev, empty, host64, lowp_close, norm_max_err
 
 pytestmark = pytest.mark.gpu
 
@@ -102,6 +102,33 @@ def test_column_sums_tall_and_wide(mdnn, shape):
     torch.cuda.synchronize()
     assert norm_max_err(host64(db), dy.astype(np.float64).sum(axis=0)) <= 1e-5
     assert torch.equal(db, db2)
+
+
+# Column sums at the edges of their passes: one launch up to 1024 rows (a row
+# lane's last rows missing), chunks of 256 above; widths one over and one under
+# the 8-column groups and the 64-column blocks, narrower than a group; bases
+# and rows on any element, NaN around them, with and without the ReLU mask.
+@pytest.mark.parametrize("shape", [(127, 9), (1024, 15), (1025, 8), (1025, 71), (5000, 65), (300, 7), (8200, 63)])
+@pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
+def test_column_sums_edges(mdnn, dt, shape):
+    import torch
+    rows, cols = shape
+    dy, y = W.normal((rows, cols), 31, 1, dt), W.normal((rows, cols), 31, 2, dt)
+
+    def place(v):
+        d = dev(v, dt).reshape(-1)
+        buf = torch.full((d.numel() + 2,), float("nan"), dtype=d.dtype, device="cuda")
+        buf[1:-1] = d
+        return buf, buf[1:-1]
+    (kd, D), (ky, Y) = place(dy), place(y)
+    nws = mdnn.mdnn_bias_act_bwd_workspace(rows, cols)
+    ws = torch.full((max(nws, 16),), 255, dtype=torch.uint8, device="cuda")
+    d64, keep = decode(dy, dt), decode(y, dt) > 0
+    for act, val in ((mdnn.ACT_NONE, d64), (mdnn.ACT_RELU, np.where(keep, d64, 0.0))):
+        db = torch.full((cols,), float("nan"), device="cuda")
+        mdnn.mdnn_bias_act_bwd(rows, cols, D, Y, act, None, db, DT[dt], ws, nws)
+        # fp32 sum of `rows` values in any order
+        assert np.all(np.abs(host64(db) - val.sum(0)) <= accum_bound(np.abs(val).sum(0), rows))
 
 
 @pytest.mark.parametrize("shape,dt", [((256, 1024), "bf16"), ((37, 72), "f16"), ((200, 77), "f32"), ((1, 8), "bf16"),
