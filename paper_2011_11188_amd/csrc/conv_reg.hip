@@ -69,8 +69,8 @@ mdnn_status_t conv_reg_fwd(const ConvGeom& g, const void* x, const void* w, cons
   const int64_t len = (int64_t)g.s * g.c, lp = round_up(len, z.E), K = g.r * lp, M = (int64_t)g.n * g.ho * g.wo;
   if (!z.ok() || !div_ok(K + 128, lp)) return MDNN_SUCCESS;
   const reg::RunArgs a{x,   (int32_t)z.x, g.r,  (int32_t)len, (int32_t)lp, magic_of(lp), g.h, g.w * g.c, g.c,
-                       g.ho, g.wo,        g.pad, g.pad,        0,           0,            M};
-  const reg::RunArgs b{w, (int32_t)z.w, g.r, (int32_t)len, (int32_t)lp, magic_of(lp), 0, 0, 0, 0, 0, 0, 0, 0, 0, g.k};
+                       g.ho, g.wo,        g.pad, g.pad,        0,           M};
+  const reg::RunArgs b{w, (int32_t)z.w, g.r, (int32_t)len, (int32_t)lp, magic_of(lp), 0, 0, 0, 0, 0, 0, 0, 0, g.k};
   MDNN_TRY((run_typed<reg::RunRowsLoader, reg::RunFilterLoader>(a, b, M, g.k, K, ep, io, out, st)));
   *done = true;
   return MDNN_SUCCESS;
@@ -83,9 +83,9 @@ mdnn_status_t conv_reg_bwd_data(const ConvGeom& g, const void* dy, const void* w
   const int64_t len = (int64_t)g.s * g.k, lp = round_up(len, z.E), K = g.r * lp, M = (int64_t)g.n * g.h * g.w;
   if (!z.ok() || !div_ok(K + 128, lp) || !div_ok(lp, g.k)) return MDNN_SUCCESS;
   const reg::RunArgs a{dy,  (int32_t)z.y, g.r,           (int32_t)len,    (int32_t)lp, magic_of(lp), g.ho, g.wo * g.k, g.k,
-                       g.h, g.w,          g.r - 1 - g.pad, g.s - 1 - g.pad, 0,           0,            M};
+                       g.h, g.w,          g.r - 1 - g.pad, g.s - 1 - g.pad, 0,           M};
   const reg::RunArgs b{w, (int32_t)z.w, g.r, (int32_t)len, (int32_t)lp,      magic_of(lp), g.k, g.s,
-                       g.c, 0,          0,   0,            0,                magic_of(g.k), 0,   0};
+                       g.c, 0,          0,   0,            0,                magic_of(g.k), 0};
   MDNN_TRY((run_typed<reg::RunRowsLoader, reg::RunFilterTLoader>(a, b, M, g.c, K, ep, io, out, st)));
   *done = true;
   return MDNN_SUCCESS;
@@ -96,7 +96,7 @@ SplitPlan conv_reg_filter_plan(const ConvGeom& g, mdnn_dtype_t io) {
   const Sizes z(g, io);
   const int64_t len = (int64_t)g.s * g.c, lp = round_up(len, z.E), M = g.k, N = g.r * lp,
                 K = (int64_t)g.n * g.ho * g.wo, bk = 8 * z.E;
-  if (!z.ok() || M < z.E || N >= LIM || !div_ok(K + 128, g.wo) || !div_ok((K + 128) / g.wo + 1, g.ho)) return p;
+  if (!z.ok() || M < z.E || N >= LIM || K + 128 >= LIM) return p;
   // about 512 workgroups (two per CU), each split at least four steps deep
   const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64), steps = ceil_div(K, bk);
   if (tiles > 0x7fffffffLL) return p;
@@ -133,7 +133,7 @@ mdnn_status_t conv_reg_bwd_filter(const ConvGeom& g, const void* x, const void* 
                 K = (int64_t)g.n * g.ho * g.wo;
   const reg::MatArgs a{dy, g.k, g.k, K};
   const reg::RunArgs b{x,    (int32_t)z.x, g.r,   (int32_t)len, (int32_t)lp,     magic_of(lp),    g.h, g.w * g.c, g.c,
-                       g.ho, g.wo,         g.pad, g.pad,        magic_of(g.wo), magic_of(g.ho), 0};
+                       g.ho, g.wo,         g.pad, g.pad,        0,               0};
   Epilogue ep{};
   ep.alpha = 1.0f;
   ep.D = dw;

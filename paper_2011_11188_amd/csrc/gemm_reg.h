@@ -15,8 +15,8 @@
 // Every load stays inside the operand: a chunk that would run past the end
 // starts earlier and is shifted into place, and elements outside the valid
 // range (k past the end, zero padding of an image) are cleared, both in
-// registers before the LDS write and only where a step can hold such a chunk
-// (the loaders' `plain` and `fx`).  Chunks past M or N of an operand whose contiguous dimension
+// registers before the LDS write and only in waves that hold such a chunk
+// (Fix).  Chunks past M or N of an operand whose contiguous dimension
 // is M or N are fetched from inside the row: they feed outputs that are
 // never stored.
 //
@@ -59,31 +59,44 @@ __device__ __forceinline__ uint4 load_chunk(const char* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// How a loaded chunk becomes the wanted one: element e of it is loaded
-// element e + d, cleared unless lo <= e < hi.
-__device__ __forceinline__ uint32_t fixup(int d, int lo, int hi) {
-  return (uint32_t)(d + 16) | ((uint32_t)lo << 8) | ((uint32_t)hi << 16);
+// How loaded chunks become the wanted ones: chunk i keeps the elements whose
+// bits are set in byte i of `keep` (all: keep_all), and where some lane of the
+// wave has a chunk at the operand's end (`shift`, uniform) element e of it is
+// loaded element e + d, d from the loader.
+struct Fix {
+  uint32_t keep;
+  bool shift;
+};
+template <int E, int L>
+constexpr uint32_t keep_all() {
+  uint32_t k = 0;
+  for (int i = 0; i < L; ++i) k |= ((1u << E) - 1u) << (8 * i);
+  return k;
+}
+// bits lo .. hi - 1
+__device__ __forceinline__ uint32_t keep_bits(int lo, int hi) {
+  return lo < hi ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
 }
 template <int ES>
-__device__ __forceinline__ uint4 apply_fix(uint4 v, uint32_t fx) {
-  const int d = (int)(fx & 0xffu) - 16, lo = (int)((fx >> 8) & 0xffu), hi = (int)((fx >> 16) & 0xffu);
-  if (__any(d != 0)) {
-    constexpr int B = 8 * ES;
-    typedef unsigned __int128 u128;
-    u128 x = ((u128)(((uint64_t)v.w << 32) | v.z) << 64) | (((uint64_t)v.y << 32) | v.x);
-    x = d >= 0 ? x >> (B * (d & 15)) : x << (B * (-d & 15));
-    const uint64_t l = (uint64_t)x, h = (uint64_t)(x >> 64);
-    v = make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
-  }
-  const int bits = lo < hi ? (int)(((1u << hi) - 1u) & ~((1u << lo) - 1u)) : 0;  // valid elements
+__device__ __forceinline__ uint4 shift_chunk(uint4 v, int d) {
+  constexpr int B = 8 * ES;
+  typedef unsigned __int128 u128;
+  u128 x = ((u128)(((uint64_t)v.w << 32) | v.z) << 64) | (((uint64_t)v.y << 32) | v.x);
+  x = d >= 0 ? x >> (B * (d & 15)) : x << (B * (-d & 15));
+  const uint64_t l = (uint64_t)x, h = (uint64_t)(x >> 64);
+  return make_uint4((uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32));
+}
+template <int ES>
+__device__ __forceinline__ uint4 keep_chunk(uint4 v, uint32_t keep, int i) {
   uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     if constexpr (ES == 2) {
-      const uint32_t a = (uint32_t)__builtin_amdgcn_sbfe(bits, 2 * j, 1), b = (uint32_t)__builtin_amdgcn_sbfe(bits, 2 * j + 1, 1);
+      const uint32_t a = (uint32_t)__builtin_amdgcn_sbfe((int)keep, 8 * i + 2 * j, 1),
+                     b = (uint32_t)__builtin_amdgcn_sbfe((int)keep, 8 * i + 2 * j + 1, 1);
       w[j] &= __builtin_amdgcn_perm(b, a, 0x05040100u);
     } else {
-      w[j] &= (uint32_t)__builtin_amdgcn_sbfe(bits, j, 1);
+      w[j] &= (uint32_t)__builtin_amdgcn_sbfe((int)keep, 8 * i + j, 1);
     }
   }
   return make_uint4(w[0], w[1], w[2], w[3]);
@@ -118,7 +131,7 @@ struct MatArgs {
 template <class T, bool KC_, int W, int L>
 struct MatLoader {
   static constexpr bool KC = KC_;
-  static constexpr bool ANY_STEP = false;  // chunks to fix only in the last step
+  static constexpr bool ANY_STEP = false;  // only the last step's chunks may need fixing
   static constexpr bool RUNS = false;      // the operand's columns are the product's
   static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
   typedef MatArgs Args;
@@ -151,7 +164,7 @@ struct MatLoader {
   }
   // CHECK = false: a step before the last
   template <bool CHECK>
-  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix&) {
     const char* kb = base + (int64_t)t * step;
     if (!CHECK || t < last) {
 #pragma unroll
@@ -160,24 +173,25 @@ struct MatLoader {
     }
     // the last step: chunks past the operand's end are fetched from inside it
 #pragma unroll
-    for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + ((int64_t)off[i] - (int64_t)back(t, i) * ES));
+    for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + ((int64_t)off[i] - shift(t, i) * ES));
+  }
+  __device__ __forceinline__ void fix(int t, Fix& f) {
+    bool any = false;
+    f.keep = 0;
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+      const int64_t left = kend - (kbeg + (int64_t)t * BK + kpos[i]);
+      f.keep |= keep_bits(0, left <= 0 ? 0 : !KC || left > E ? E : (int)left) << (8 * i);
+      any |= shift(t, i) != 0;
+    }
+    f.shift = __any(any);
   }
   // elements that chunk i of the last step is fetched early by
-  __device__ __forceinline__ int64_t back(int t, int i) {
+  __device__ __forceinline__ int64_t shift(int t, int i) {
     const int64_t k0 = kbeg + (int64_t)t * BK;
-    if constexpr (KC) {
-      const int64_t over = k0 + kpos[i] + E - K;
-      return over > 0 ? over : 0;
-    } else {
-      const int64_t over = (int64_t)(off[i] / ES) - ((K - 1 - k0) * ld + MN - E);
-      return over > 0 ? over : 0;
-    }
-  }
-  __device__ __forceinline__ bool plain(int t) { return t < last; }
-  __device__ __forceinline__ uint32_t fx(int t, int i) {
-    const int64_t left = kend - (kbeg + (int64_t)t * BK + kpos[i]);
-    const int hi = left <= 0 ? 0 : !KC || left > E ? E : (int)left;
-    return fixup(hi ? (int)back(t, i) : 0, 0, hi);
+    const int64_t over =
+        KC ? k0 + kpos[i] + E - K : (int64_t)(off[i] / ES) - ((K - 1 - k0) * ld + MN - E);
+    return over > 0 ? over : 0;
   }
 };
 
@@ -198,21 +212,18 @@ struct RunArgs {
   int32_t hs, wsC, C;      // image rows, elements per image row, channels
   int32_t ho, wo;          // output grid
   int32_t padr, pads;      // rows above, pixels left
-  uint32_t magic_a, magic_b;  // RunColsLoader: of wo, ho; RunFilterT: of the run's channels
+  uint32_t magic_a;        // RunFilterTLoader: of the filters
   int64_t M;               // output pixels (RunRowsLoader), filters (RunFilter)
 };
 
 __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
 
-// image chunk: element offset o (may lie outside), x position q of its first
-// element in the image row, e of it in the run
+// elements kept of an image chunk: x position q of its first element in the
+// image row (wsC elements), `left` elements left in the run
 template <int E>
-__device__ __forceinline__ uint32_t run_fix(bool ok, int o, int total, int q, int wsC, int left) {
-  int lo = q < 0 ? -q : 0, hi = wsC - q < left ? wsC - q : left;
-  lo = lo > E ? E : lo;
-  hi = clampi(hi, 0, E);
-  if (!ok || lo >= hi) return fixup(0, 0, 0);
-  return fixup(o - clampi(o, 0, total - E), lo, hi);
+__device__ __forceinline__ uint32_t run_keep(bool ok, int q, int wsC, int left) {
+  const int lo = q < 0 ? (q < -E ? E : -q) : 0, hi = clampi(wsC - q < left ? wsC - q : left, 0, E);
+  return ok ? keep_bits(lo, hi) : 0u;
 }
 
 // Rows = output pixels, k = (filter row, run): forward x, and dy of backward
@@ -256,22 +267,31 @@ struct RunRowsLoader {
     e = (int)k - r * lp;
   }
   template <bool CHECK>
-  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
-    int r[P], e[P];
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix& f) {
+    int r[P], e[P], rel[P];
 #pragma unroll
-    for (int q = 0; q < P; ++q) where(t, q, r[q], e[q]);
+    for (int q = 0; q < P; ++q) {
+      where(t, q, r[q], e[q]);
+      rel[q] = r[q] * wsC + e[q];
+      if (r[q] >= rows) r[q] = 1 << 24;  // past the filter: outside every image
+    }
+    bool any = false;
+    f.keep = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const int o = clampi(base[i] + r[i % P] * wsC + e[i % P], 0, total - E);
-      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+      const int par = i % P, o = base[i] + rel[par], from = clampi(o, 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)from * (uint32_t)ES);
+      const uint32_t k = run_keep<E>((uint32_t)(iy[i] + r[par]) < (uint32_t)hs, jc[i] + e[par], wsC, len - e[par]);
+      f.keep |= k << (8 * i);
+      any |= o != from && k != 0;
     }
+    f.shift = __any(any);
   }
-  __device__ __forceinline__ bool plain(int) { return false; }
-  __device__ __forceinline__ uint32_t fx(int t, int i) {
+  __device__ __forceinline__ int shift(int t, int i) {
     int r, e;
     where(t, i % P, r, e);
-    return run_fix<E>(r < rows && (uint32_t)(iy[i] + r) < (uint32_t)hs, base[i] + r * wsC + e, total, jc[i] + e, wsC,
-                      len - e);
+    const int o = base[i] + r * wsC + e;
+    return o - clampi(o, 0, total - E);
   }
 };
 
@@ -304,21 +324,32 @@ struct RunFilterLoader {
     e = (int)k - r * lp;
   }
   template <bool CHECK>
-  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
-    int r[P], e[P];
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix& f) {
+    int rel[P];
+    uint32_t k[P];
 #pragma unroll
-    for (int q = 0; q < P; ++q) where(t, q, r[q], e[q]);
+    for (int q = 0; q < P; ++q) {
+      int r, e;
+      where(t, q, r, e);
+      rel[q] = r * len + e;
+      k[q] = r < rows ? keep_bits(0, clampi(len - e, 0, E)) : 0u;
+    }
+    bool any = false;
+    f.keep = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const int o = clampi(base[i] + r[i % P] * len + e[i % P], 0, total - E);
-      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+      const int o = base[i] + rel[i % P], from = clampi(o, 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)from * (uint32_t)ES);
+      f.keep |= k[i % P] << (8 * i);
+      any |= o != from && k[i % P] != 0;
     }
+    f.shift = __any(any);
   }
-  __device__ __forceinline__ bool plain(int) { return false; }
-  __device__ __forceinline__ uint32_t fx(int t, int i) {
+  __device__ __forceinline__ int shift(int t, int i) {
     int r, e;
     where(t, i % P, r, e);
-    return run_fix<E>(r < rows, base[i] + r * len + e, total, 0, E, len - e);
+    const int o = base[i] + r * len + e;
+    return o - clampi(o, 0, total - E);
   }
 };
 
@@ -354,71 +385,109 @@ struct RunFilterTLoader {
     return r < rows && e < len;
   }
   template <bool CHECK>
-  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+  __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix& f) {
+    bool any = false;
+    f.keep = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       int o;
-      where(t, i, o);
-      o = clampi(o, 0, total - E);
-      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+      const bool ok = where(t, i, o);
+      const int from = clampi(o, 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)from * (uint32_t)ES);
+      f.keep |= (ok ? (1u << E) - 1u : 0u) << (8 * i);
+      any |= ok && o != from;
     }
+    f.shift = __any(any);
   }
-  __device__ __forceinline__ bool plain(int) { return false; }
-  __device__ __forceinline__ uint32_t fx(int t, int i) {
+  __device__ __forceinline__ int shift(int t, int i) {
     int o;
-    const bool ok = where(t, i, o);
-    return ok ? fixup(o - clampi(o, 0, total - E), 0, E) : fixup(0, 0, 0);
+    where(t, i, o);
+    return o - clampi(o, 0, total - E);
   }
 };
 
 // Shifted image columns of the filter gradient: k = output pixel, columns =
-// (filter row, padded run).
+// (filter row, padded run).  Steps are loaded in order: each lane's pixel
+// (image, row, column) moves on by one step's pixels with carries, where two
+// divisions per chunk had bound the kernel (3 channels, 7x7).
 template <class T, int W, int L>
 struct RunColsLoader {
   static constexpr bool KC = false, ANY_STEP = true, RUNS = true;
   static constexpr int ES = El<T>::ES, E = El<T>::E, BK = El<T>::BK;
   typedef RunArgs Args;
   const char* p;
-  int32_t total, hs, wsC, C, ho, wo, k0, kend;
-  uint32_t magic_w, magic_h;
-  int32_t krow[L], dy[L], dq[L], left[L];  // filter row, run position (both less the padding), elements left in the run
+  int32_t total, hs, wsC, ho, wo;
+  // per step: rows and the offset they and the columns move on by; carries
+  int32_t dj, di, doff, dqs, woC, row_gap, img_gap;
+  int32_t n0, lp, k0, padr, pads, C;  // for shift()
+  // next step's pixels left, column, row (less the padding), x position and
+  // offset of each chunk; elements left in its run
+  int32_t pleft[L], j[L], i_[L], y0[L], q[L], o[L], left[L];
 
   __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t ke, int wave, int lane) {
-    p = (const char*)a.p, total = a.total, hs = a.hs, wsC = a.wsC, C = a.C, ho = a.ho, wo = a.wo;
-    magic_w = a.magic_a, magic_h = a.magic_b, k0 = (int32_t)kb, kend = (int32_t)ke;
+    p = (const char*)a.p, total = a.total, hs = a.hs, wsC = a.wsC, ho = a.ho, wo = a.wo;
+    n0 = (int32_t)mn0, lp = a.Lp, k0 = (int32_t)kb, padr = a.padr, pads = a.pads, C = a.C;
+    const int32_t rows = BK / wo, dn = rows / ho;
+    dj = BK - rows * wo;
+    di = rows - dn * ho;
+    dqs = dj * a.C;
+    doff = (dn * hs + di) * wsC + dqs;
+    woC = wo * a.C;
+    row_gap = wsC - woC;        // a carry from the last column to the next row
+    img_gap = (hs - ho) * wsC;  // and from the last row to the next image
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const LoadPos q = load_pos<T, false, W, L>(wave, lane, i);
-      const int32_t nn = (int32_t)mn0 + q.c, r = nn / a.Lp, e = nn - r * a.Lp;
-      krow[i] = q.r;
-      dy[i] = r < a.rows ? r - a.padr : -(1 << 20);
-      dq[i] = e - a.pads * a.C;
+      const LoadPos c = load_pos<T, false, W, L>(wave, lane, i);
+      const int32_t nn = (int32_t)mn0 + c.c, r = nn / a.Lp, e = nn - r * a.Lp;
+      const int32_t px = (int32_t)kb + c.r, q1 = px / wo, n = q1 / ho;
+      pleft[i] = (int32_t)ke - px;
+      j[i] = px - q1 * wo;
+      i_[i] = q1 - n * ho;
+      y0[i] = r < a.rows ? r - a.padr : -(1 << 24);  // (outside every image)
+      q[i] = (j[i] - a.pads) * a.C + e;
       left[i] = a.L - e;
+      o[i] = (int32_t)(((uint32_t)n * (uint32_t)hs + (uint32_t)(i_[i] + r - a.padr)) * (uint32_t)wsC + (uint32_t)q[i]);
     }
-  }
-  __device__ __forceinline__ bool where(int t, int i, int& o, int& q) {
-    const uint32_t px = (uint32_t)(k0 + t * BK + krow[i]);
-    const uint32_t q1 = fast_div(px, magic_w), q2 = fast_div(q1, magic_h);
-    const int y = (int)(q1 - q2 * (uint32_t)ho) + dy[i];
-    q = (int)(px - q1 * (uint32_t)wo) * C + dq[i];
-    o = (int)((q2 * (uint32_t)hs + (uint32_t)y) * (uint32_t)wsC + (uint32_t)q);  // (used only inside the image)
-    return (int)px < kend && (uint32_t)y < (uint32_t)hs;
   }
   template <bool CHECK>
-  __device__ __forceinline__ void load(int t, uint4 (&v)[L]) {
+  __device__ __forceinline__ void load(int, uint4 (&v)[L], Fix& f) {
+    bool any = false;
+    f.keep = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      int o, q;
-      const bool ok = where(t, i, o, q);
-      o = ok ? clampi(o, 0, total - E) : 0;
-      v[i] = load_chunk<ES>(p + (uint32_t)o * (uint32_t)ES);
+      const uint32_t k = run_keep<E>(pleft[i] > 0 && (uint32_t)(i_[i] + y0[i]) < (uint32_t)hs, q[i], wsC, left[i]);
+      const int from = clampi(o[i], 0, total - E);
+      v[i] = load_chunk<ES>(p + (uint32_t)from * (uint32_t)ES);
+      f.keep |= k << (8 * i);
+      any |= o[i] != from && k != 0;
+      pleft[i] -= BK;
+      j[i] += dj;
+      q[i] += dqs;
+      o[i] += doff;
+      i_[i] += di;
+      if (j[i] >= wo) {
+        j[i] -= wo;
+        q[i] -= woC;
+        o[i] += row_gap;
+        ++i_[i];
+      }
+      if (i_[i] >= ho) {
+        i_[i] -= ho;
+        o[i] += img_gap;
+      }
     }
+    f.shift = __any(any);
   }
-  __device__ __forceinline__ bool plain(int) { return false; }
-  __device__ __forceinline__ uint32_t fx(int t, int i) {
-    int o, q;
-    const bool ok = where(t, i, o, q);
-    return run_fix<E>(ok, o, total, q, wsC, left[i]);
+  // (rare: the first and last pixels' chunks) the offset again, by division
+  __device__ __forceinline__ int shift(int t, int i) {
+    const LoadPos c =
+        load_pos<T, false, W, L>(__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), (int)threadIdx.x & 63, i);
+    const int32_t nn = n0 + c.c, r = nn / lp, e = nn - r * lp;
+    const int32_t px = k0 + t * BK + c.r, q1 = px / wo, n = q1 / ho;
+    const int32_t at = (int32_t)(((uint32_t)n * (uint32_t)hs + (uint32_t)(q1 - n * ho + r - padr)) * (uint32_t)wsC +
+                                 (uint32_t)((px - q1 * wo - pads) * C + e));
+    const int32_t d = at - clampi(at, 0, total - E);
+    return d > -E && d < E ? d : 0;  // (further off: nothing of the chunk is kept)
   }
 };
 
@@ -477,34 +546,38 @@ __device__ __forceinline__ void mfma_step(const uint4 (&a)[FM], const uint4 (&b)
 template <class T, class TL, int NR>
 struct Sets {
   uint4 a[NR][TL::LA], b[NR][TL::LB];
+  Fix fa[NR], fb[NR];
 };
 
-// Tile t of one operand: registers -> LDS.
-template <int ES, bool CHECK, class Loader, int L>
-__device__ __forceinline__ void commit(char* dst, int t, const uint4 (&v)[L], Loader& ld) {
-  if constexpr (Loader::ANY_STEP) {
-    // image edges turn up in any step: test this wave's chunks
-    uint32_t fx[L];
-    bool need = false;
+template <int ES, class Loader, int L>
+__device__ __forceinline__ void commit_fixed(char* dst, int t, const uint4 (&v)[L], const Fix& f, Loader& ld) {
 #pragma unroll
-    for (int i = 0; i < L; ++i) {
-      fx[i] = ld.fx(t, i);
-      need |= fx[i] != fixup(0, 0, 16 / ES);
-    }
-    if (__any(need)) {
-#pragma unroll
-      for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = apply_fix<ES>(v[i], fx[i]);
-    } else {
-#pragma unroll
-      for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = v[i];
-    }
-  } else if (!CHECK || ld.plain(t)) {
-#pragma unroll
-    for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = v[i];
-  } else {
-#pragma unroll
-    for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = apply_fix<ES>(v[i], ld.fx(t, i));
+  for (int i = 0; i < L; ++i) {
+    uint4 c = v[i];
+    if (f.shift) c = shift_chunk<ES>(c, (int)ld.shift(t, i));
+    *(uint4*)(dst + i * 1024) = keep_chunk<ES>(c, f.keep, i);
   }
+}
+// Tile t of one operand: registers -> LDS.  A loader that may need to fix
+// any step's chunks (image edges) is tested per wave; a plain matrix fixes
+// its last step's.
+template <int ES, bool CHECK, class Loader, int L>
+__device__ __forceinline__ void commit(char* dst, int t, const uint4 (&v)[L], const Fix& f, Loader& ld) {
+  if constexpr (Loader::ANY_STEP) {
+    if (__any(f.keep != keep_all<16 / ES, L>()) || f.shift) {
+      commit_fixed<ES>(dst, t, v, f, ld);
+      return;
+    }
+  } else if constexpr (CHECK) {
+    if (t == ld.last) {
+      Fix last;
+      ld.fix(t, last);
+      commit_fixed<ES>(dst, t, v, last, ld);
+      return;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = v[i];
 }
 
 // Steps t + J .. t + U - 1 of one unrolled round; tile t + J is in LDS stage
@@ -518,8 +591,8 @@ __device__ __forceinline__ void steps(int t, int nk, char* const (&sa)[2], char*
     if (CHECK && t + J >= nk) return;
     constexpr int S = J % NR, S1 = (J + 1) % NR;
     if (!CHECK || t + J + NR < nk) {
-      la.template load<CHECK>(t + J + NR, s.a[S]);
-      lb.template load<CHECK>(t + J + NR, s.b[S]);
+      la.template load<CHECK>(t + J + NR, s.a[S], s.fa[S]);
+      lb.template load<CHECK>(t + J + NR, s.b[S], s.fb[S]);
     }
     const char* ta = sa[J & 1];
     const char* tb = sb[J & 1];
@@ -535,8 +608,8 @@ __device__ __forceinline__ void steps(int t, int nk, char* const (&sa)[2], char*
     mfma_step<T, NA>(a0, b0, acc);
     mfma_step<T, NA>(a1, b1, acc);
     if (!CHECK || t + J + 1 < nk) {
-      commit<El<T>::ES, CHECK>(sa[(J + 1) & 1] + wa, t + J + 1, s.a[S1], la);
-      commit<El<T>::ES, CHECK>(sb[(J + 1) & 1] + wb, t + J + 1, s.b[S1], lb);
+      commit<El<T>::ES, CHECK>(sa[(J + 1) & 1] + wa, t + J + 1, s.a[S1], s.fa[S1], la);
+      commit<El<T>::ES, CHECK>(sb[(J + 1) & 1] + wb, t + J + 1, s.b[S1], s.fb[S1], lb);
     }
     __syncthreads();
     steps<T, TL, NR, LA, LB, J + 1, U, CHECK, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, acc);
@@ -591,12 +664,12 @@ gemm_reg_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
 #pragma unroll
   for (int r = 0; r < NR; ++r)
     if (r < nk) {
-      la.template load<true>(r, s.a[r]);
-      lb.template load<true>(r, s.b[r]);
+      la.template load<true>(r, s.a[r], s.fa[r]);
+      lb.template load<true>(r, s.b[r], s.fb[r]);
     }
   if (nk > 0) {
-    commit<ES, true>(sa[0] + wa, 0, s.a[0], la);
-    commit<ES, true>(sb[0] + wb, 0, s.b[0], lb);
+    commit<ES, true>(sa[0] + wa, 0, s.a[0], s.fa[0], la);
+    commit<ES, true>(sb[0] + wb, 0, s.b[0], s.fb[0], lb);
   }
   __syncthreads();
   constexpr int U = NR % 2 == 0 ? NR : 2 * NR;
