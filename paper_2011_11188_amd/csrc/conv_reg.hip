@@ -97,10 +97,12 @@ SplitPlan conv_reg_filter_plan(const ConvGeom& g, mdnn_dtype_t io) {
   const int64_t len = (int64_t)g.s * g.c, lp = round_up(len, z.E), M = g.k, N = g.r * lp,
                 K = (int64_t)g.n * g.ho * g.wo, bk = 8 * z.E;
   if (!z.ok() || M < z.E || N >= LIM || K + 128 >= LIM) return p;
-  // about 512 workgroups (two per CU), each split at least four steps deep
+  // at most 512 workgroups, which is two per CU at once (one more would run
+  // alone after them: 513 took 41 us where 510 take 34), each split at least
+  // four steps deep
   const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64), steps = ceil_div(K, bk);
   if (tiles > 0x7fffffffLL) return p;
-  int64_t s = ceil_div(512, tiles);
+  int64_t s = 512 / tiles;
   if (s > steps / 4) s = steps / 4;
   while (s > 1 && (size_t)s * z.w * 4 > FILTER_WS_MAX) --s;
   if (s < 1) s = 1;

@@ -1020,10 +1020,7 @@ gemm_lds_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
     epilogue_interior<T, OutT, FM, FN>(ep, M, N, mb, nb, acc);
     return;
   }
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) epilogue_store4<T, OutT>(ep, M, N, mb + i * 16, nb + j * 16, acc[i][j]);
+  epilogue_any<T, OutT, FM, FN>(ep, M, N, mb, nb, acc);
 }
 
 // Plain-GEMM configurations: 256 x 256 tile with 8 waves of 128 x 64, and

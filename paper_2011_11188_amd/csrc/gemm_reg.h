@@ -67,6 +67,11 @@ struct Fix {
   uint32_t keep;
   bool shift;
 };
+// The last step's: also each chunk's d, a byte each (d + 16).
+struct LastFix {
+  uint32_t keep, shift;
+};
+__device__ __forceinline__ uint32_t pack_shift(int d, int i) { return (uint32_t)(d + 16) << (8 * i); }
 template <int E, int L>
 constexpr uint32_t keep_all() {
   uint32_t k = 0;
@@ -137,13 +142,11 @@ struct MatLoader {
   typedef MatArgs Args;
   const char* base;
   int64_t step, ld, MN, K, kbeg, kend;
-  int32_t last;  // the step that ends at kend
   uint32_t off[L];
   int32_t kpos[L];  // KC: k of the chunk within a step; else its k-row
 
   __device__ __forceinline__ void init(const MatArgs& a, int64_t mn0, int64_t kb, int64_t ke, int wave, int lane) {
     ld = a.ld, MN = a.MN, K = a.K, kbeg = kb, kend = ke;
-    last = (int32_t)((ke - kb + BK - 1) / BK) - 1;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
       const LoadPos q = load_pos<T, KC, W, L>(wave, lane, i);
@@ -162,36 +165,24 @@ struct MatLoader {
     step = (KC ? (int64_t)BK : BK * ld) * ES;
     base = (const char*)a.p + (KC ? kbeg : kbeg * ld) * ES;
   }
-  // CHECK = false: a step before the last
-  template <bool CHECK>
   __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix&) {
     const char* kb = base + (int64_t)t * step;
-    if (!CHECK || t < last) {
 #pragma unroll
-      for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + off[i]);
-      return;
-    }
-    // the last step: chunks past the operand's end are fetched from inside it
-#pragma unroll
-    for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + ((int64_t)off[i] - shift(t, i) * ES));
+    for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + off[i]);
   }
-  __device__ __forceinline__ void fix(int t, Fix& f) {
-    bool any = false;
-    f.keep = 0;
+  // the last step (from kbeg): k past kend is cleared, chunks past the
+  // operand's end are fetched from inside it
+  __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) {
+    f.keep = f.shift = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const int64_t left = kend - (kbeg + (int64_t)t * BK + kpos[i]);
-      f.keep |= keep_bits(0, left <= 0 ? 0 : !KC || left > E ? E : (int)left) << (8 * i);
-      any |= shift(t, i) != 0;
+      const int64_t over = KC ? kbeg + kpos[i] + E - K : (int64_t)(off[i] / ES) - ((K - 1 - kbeg) * ld + MN - E);
+      const int64_t d = over > 0 ? over : 0, left = kend - (kbeg + kpos[i]);
+      v[i] = load_chunk<ES>(base + ((int64_t)off[i] - d * ES));
+      const int hi = left <= 0 ? 0 : !KC || left > E ? E : (int)left;
+      f.keep |= keep_bits(0, hi) << (8 * i);
+      f.shift |= pack_shift(hi ? (int)d : 0, i);
     }
-    f.shift = __any(any);
-  }
-  // elements that chunk i of the last step is fetched early by
-  __device__ __forceinline__ int64_t shift(int t, int i) {
-    const int64_t k0 = kbeg + (int64_t)t * BK;
-    const int64_t over =
-        KC ? k0 + kpos[i] + E - K : (int64_t)(off[i] / ES) - ((K - 1 - k0) * ld + MN - E);
-    return over > 0 ? over : 0;
   }
 };
 
@@ -224,6 +215,20 @@ template <int E>
 __device__ __forceinline__ uint32_t run_keep(bool ok, int q, int wsC, int left) {
   const int lo = q < 0 ? (q < -E ? E : -q) : 0, hi = clampi(wsC - q < left ? wsC - q : left, 0, E);
   return ok ? keep_bits(lo, hi) : 0u;
+}
+
+// the last step of a run loader (set up at that step)
+template <class Loader, int L>
+__device__ __forceinline__ void run_load_last(Loader& ld, uint4 (&v)[L], LastFix& f) {
+  Fix g;
+  ld.load(0, v, g);
+  f.keep = g.keep;
+  f.shift = 0;
+#pragma unroll
+  for (int i = 0; i < L; ++i) {
+    const int d = (int)ld.shift(0, i);
+    f.shift |= pack_shift(d > -Loader::E && d < Loader::E ? d : 0, i);
+  }
 }
 
 // Rows = output pixels, k = (filter row, run): forward x, and dy of backward
@@ -266,7 +271,6 @@ struct RunRowsLoader {
     r = (int)fast_div(k, magic);
     e = (int)k - r * lp;
   }
-  template <bool CHECK>
   __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix& f) {
     int r[P], e[P], rel[P];
 #pragma unroll
@@ -287,6 +291,7 @@ struct RunRowsLoader {
     }
     f.shift = __any(any);
   }
+  __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
   __device__ __forceinline__ int shift(int t, int i) {
     int r, e;
     where(t, i % P, r, e);
@@ -323,7 +328,6 @@ struct RunFilterLoader {
     r = (int)fast_div(k, magic);
     e = (int)k - r * lp;
   }
-  template <bool CHECK>
   __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix& f) {
     int rel[P];
     uint32_t k[P];
@@ -345,6 +349,7 @@ struct RunFilterLoader {
     }
     f.shift = __any(any);
   }
+  __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
   __device__ __forceinline__ int shift(int t, int i) {
     int r, e;
     where(t, i % P, r, e);
@@ -384,7 +389,6 @@ struct RunFilterTLoader {
     o = ((f * rows + rows - 1 - r) * S + S - 1 - s) * C + col[i];
     return r < rows && e < len;
   }
-  template <bool CHECK>
   __device__ __forceinline__ void load(int t, uint4 (&v)[L], Fix& f) {
     bool any = false;
     f.keep = 0;
@@ -399,6 +403,7 @@ struct RunFilterTLoader {
     }
     f.shift = __any(any);
   }
+  __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
   __device__ __forceinline__ int shift(int t, int i) {
     int o;
     where(t, i, o);
@@ -449,7 +454,6 @@ struct RunColsLoader {
       o[i] = (int32_t)(((uint32_t)n * (uint32_t)hs + (uint32_t)(i_[i] + r - a.padr)) * (uint32_t)wsC + (uint32_t)q[i]);
     }
   }
-  template <bool CHECK>
   __device__ __forceinline__ void load(int, uint4 (&v)[L], Fix& f) {
     bool any = false;
     f.keep = 0;
@@ -478,6 +482,7 @@ struct RunColsLoader {
     }
     f.shift = __any(any);
   }
+  __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
   // (rare: the first and last pixels' chunks) the offset again, by division
   __device__ __forceinline__ int shift(int t, int i) {
     const LoadPos c =
@@ -549,70 +554,73 @@ struct Sets {
   Fix fa[NR], fb[NR];
 };
 
-template <int ES, class Loader, int L>
-__device__ __forceinline__ void commit_fixed(char* dst, int t, const uint4 (&v)[L], const Fix& f, Loader& ld) {
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    uint4 c = v[i];
-    if (f.shift) c = shift_chunk<ES>(c, (int)ld.shift(t, i));
-    *(uint4*)(dst + i * 1024) = keep_chunk<ES>(c, f.keep, i);
-  }
-}
 // Tile t of one operand: registers -> LDS.  A loader that may need to fix
-// any step's chunks (image edges) is tested per wave; a plain matrix fixes
-// its last step's.
-template <int ES, bool CHECK, class Loader, int L>
+// any step's chunks (image edges) is tested per wave.
+template <int ES, class Loader, int L>
 __device__ __forceinline__ void commit(char* dst, int t, const uint4 (&v)[L], const Fix& f, Loader& ld) {
   if constexpr (Loader::ANY_STEP) {
     if (__any(f.keep != keep_all<16 / ES, L>()) || f.shift) {
-      commit_fixed<ES>(dst, t, v, f, ld);
-      return;
-    }
-  } else if constexpr (CHECK) {
-    if (t == ld.last) {
-      Fix last;
-      ld.fix(t, last);
-      commit_fixed<ES>(dst, t, v, last, ld);
+#pragma unroll
+      for (int i = 0; i < L; ++i) {
+        uint4 c = v[i];
+        if (f.shift) c = shift_chunk<ES>(c, (int)ld.shift(t, i));
+        *(uint4*)(dst + i * 1024) = keep_chunk<ES>(c, f.keep, i);
+      }
       return;
     }
   }
 #pragma unroll
   for (int i = 0; i < L; ++i) *(uint4*)(dst + i * 1024) = v[i];
 }
+template <int ES, int L>
+__device__ __forceinline__ void commit_last(char* dst, const uint4 (&v)[L], const LastFix& f) {
+#pragma unroll
+  for (int i = 0; i < L; ++i) {
+    uint4 c = v[i];
+    const int d = (int)((f.shift >> (8 * i)) & 0xffu) - 16;
+    if (__any(d != 0)) c = shift_chunk<ES>(c, d);
+    *(uint4*)(dst + i * 1024) = keep_chunk<ES>(c, f.keep, i);
+  }
+}
+
+// The products of the tile in one LDS stage.
+template <class T, class TL, class LA, class LB, int NA>
+__device__ __forceinline__ void tile_products(const char* ta, const char* tb, int wm, int wn, const lds::LaneFrag& fa,
+                                              const lds::LaneFrag& fb, float4_t (&acc)[NA][TL::FM][TL::FN]) {
+  uint4 a0[TL::FM], b0[TL::FN], a1[TL::FM], b1[TL::FN];
+#pragma unroll
+  for (int i = 0; i < TL::FM; ++i) a0[i] = fragment<T, LA::KC, TL::BM>(ta, wm * TL::WTM + i * 16, 0, fa);
+#pragma unroll
+  for (int j = 0; j < TL::FN; ++j) b0[j] = fragment<T, LB::KC, TL::BN>(tb, wn * TL::WTN + j * 16, 0, fb);
+#pragma unroll
+  for (int i = 0; i < TL::FM; ++i) a1[i] = fragment<T, LA::KC, TL::BM>(ta, wm * TL::WTM + i * 16, 1, fa);
+#pragma unroll
+  for (int j = 0; j < TL::FN; ++j) b1[j] = fragment<T, LB::KC, TL::BN>(tb, wn * TL::WTN + j * 16, 1, fb);
+  mfma_step<T, NA>(a0, b0, acc);
+  mfma_step<T, NA>(a1, b1, acc);
+}
 
 // Steps t + J .. t + U - 1 of one unrolled round; tile t + J is in LDS stage
 // J % 2, the tiles after it in register sets (J + 1) % NR, ...
-// CHECK = false: every tile loaded in the round comes before the last one.
+// CHECK = false: the round's loads and tiles all exist.
 template <class T, class TL, int NR, class LA, class LB, int J, int U, bool CHECK, int NA>
-__device__ __forceinline__ void steps(int t, int nk, char* const (&sa)[2], char* const (&sb)[2], uint32_t wa,
+__device__ __forceinline__ void steps(int t, int n1, char* const (&sa)[2], char* const (&sb)[2], uint32_t wa,
                                       uint32_t wb, int wm, int wn, const lds::LaneFrag& fa, const lds::LaneFrag& fb,
                                       LA& la, LB& lb, Sets<T, TL, NR>& s, float4_t (&acc)[NA][TL::FM][TL::FN]) {
   if constexpr (J < U) {
-    if (CHECK && t + J >= nk) return;
+    if (CHECK && t + J >= n1) return;
     constexpr int S = J % NR, S1 = (J + 1) % NR;
-    if (!CHECK || t + J + NR < nk) {
-      la.template load<CHECK>(t + J + NR, s.a[S], s.fa[S]);
-      lb.template load<CHECK>(t + J + NR, s.b[S], s.fb[S]);
+    if (!CHECK || t + J + NR < n1) {
+      la.load(t + J + NR, s.a[S], s.fa[S]);
+      lb.load(t + J + NR, s.b[S], s.fb[S]);
     }
-    const char* ta = sa[J & 1];
-    const char* tb = sb[J & 1];
-    uint4 a0[TL::FM], b0[TL::FN], a1[TL::FM], b1[TL::FN];
-#pragma unroll
-    for (int i = 0; i < TL::FM; ++i) a0[i] = fragment<T, LA::KC, TL::BM>(ta, wm * TL::WTM + i * 16, 0, fa);
-#pragma unroll
-    for (int j = 0; j < TL::FN; ++j) b0[j] = fragment<T, LB::KC, TL::BN>(tb, wn * TL::WTN + j * 16, 0, fb);
-#pragma unroll
-    for (int i = 0; i < TL::FM; ++i) a1[i] = fragment<T, LA::KC, TL::BM>(ta, wm * TL::WTM + i * 16, 1, fa);
-#pragma unroll
-    for (int j = 0; j < TL::FN; ++j) b1[j] = fragment<T, LB::KC, TL::BN>(tb, wn * TL::WTN + j * 16, 1, fb);
-    mfma_step<T, NA>(a0, b0, acc);
-    mfma_step<T, NA>(a1, b1, acc);
-    if (!CHECK || t + J + 1 < nk) {
-      commit<El<T>::ES, CHECK>(sa[(J + 1) & 1] + wa, t + J + 1, s.a[S1], s.fa[S1], la);
-      commit<El<T>::ES, CHECK>(sb[(J + 1) & 1] + wb, t + J + 1, s.b[S1], s.fb[S1], lb);
+    tile_products<T, TL, LA, LB, NA>(sa[J & 1], sb[J & 1], wm, wn, fa, fb, acc);
+    if (!CHECK || t + J + 1 < n1) {
+      commit<El<T>::ES>(sa[(J + 1) & 1] + wa, t + J + 1, s.a[S1], s.fa[S1], la);
+      commit<El<T>::ES>(sb[(J + 1) & 1] + wb, t + J + 1, s.b[S1], s.fb[S1], lb);
     }
     __syncthreads();
-    steps<T, TL, NR, LA, LB, J + 1, U, CHECK, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, acc);
+    steps<T, TL, NR, LA, LB, J + 1, U, CHECK, NA>(t, n1, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, acc);
   }
 }
 
@@ -660,24 +668,54 @@ gemm_reg_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
 #pragma unroll
       for (int j = 0; j < FN; ++j) accs[q][i][j] = (float4_t){0.f, 0.f, 0.f, 0.f};
 
+  // Tiles 0 .. n1 - 1 are pipelined; the last one, which may end inside a step
+  // and at the operands' ends, is fetched beside the final rounds and
+  // multiplied after them, so that only it carries the code for that (code of
+  // 38-95 KB was 14-34 KB without it in every round: 1000 x 777 x 1531 bf16
+  // 17.7 -> 15.4 us).  Two loaders that fix any step's chunks need no such step.
+  constexpr bool LAST = !(LA::ANY_STEP && LB::ANY_STEP);
+  const int n1 = LAST ? nk - 1 : nk;
   Sets<T, TL, NR> s;
 #pragma unroll
   for (int r = 0; r < NR; ++r)
-    if (r < nk) {
-      la.template load<true>(r, s.a[r], s.fa[r]);
-      lb.template load<true>(r, s.b[r], s.fb[r]);
+    if (r < n1) {
+      la.load(r, s.a[r], s.fa[r]);
+      lb.load(r, s.b[r], s.fb[r]);
     }
-  if (nk > 0) {
-    commit<ES, true>(sa[0] + wa, 0, s.a[0], s.fa[0], la);
-    commit<ES, true>(sb[0] + wb, 0, s.b[0], s.fb[0], lb);
+  if (n1 > 0) {
+    commit<ES>(sa[0] + wa, 0, s.a[0], s.fa[0], la);
+    commit<ES>(sb[0] + wb, 0, s.b[0], s.fb[0], lb);
   }
   __syncthreads();
   constexpr int U = NR % 2 == 0 ? NR : 2 * NR;
   int t = 0;
-  for (; t + U + NR < nk; t += U)
-    steps<T, TL, NR, LA, LB, 0, U, false, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);
-  for (; t < nk; t += U)
-    steps<T, TL, NR, LA, LB, 0, U, true, NA>(t, nk, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);
+  // Everything fetched so far has landed before the steady loop: with loads of
+  // the branches above outstanding at its head the compiler waits there for
+  // every load in flight, once per round (fp32 NN 1024 x 2048 x 2048: 87 -> 77 us).
+  if (U + NR <= n1) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+  for (; t + U + NR <= n1; t += U)
+    steps<T, TL, NR, LA, LB, 0, U, false, NA>(t, n1, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);
+  uint4 za[TL::LA], zb[TL::LB];
+  LastFix ga, gb;
+  if (LAST && nk > 0) {
+    const int64_t kz = kbeg + (int64_t)n1 * BK;
+    LA qa;
+    LB qb;
+    qa.init(aa, m0, kz, kend, wave, lane);
+    qb.init(ba, n0, kz, kend, wave, lane);
+    qa.load_last(za, ga);
+    qb.load_last(zb, gb);
+  }
+  for (; t < n1; t += U)
+    steps<T, TL, NR, LA, LB, 0, U, true, NA>(t, n1, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);
+  if (LAST && nk > 0) {
+    char* const ta = n1 & 1 ? sa[1] : sa[0];
+    char* const tb = n1 & 1 ? sb[1] : sb[0];
+    commit_last<ES>(ta + wa, za, ga);
+    commit_last<ES>(tb + wb, zb, gb);
+    __syncthreads();
+    tile_products<T, TL, LA, LB, NA>(ta, tb, wm, wn, fa, fb, accs);
+  }
   float4_t(&acc)[FM][FN] = accs[0];
   if constexpr (NA == 4) {
 #pragma unroll
@@ -733,21 +771,7 @@ gemm_reg_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
       }
     return;
   }
-  if (full_tile_epilogue(ep, m0 + TL::BM <= M && n0 + TL::BN <= N, N)) {
-    if constexpr (ES == 2) {
-      epilogue_interior<T, OutT, FM, FN>(ep, M, N, mb, nb, acc);
-    } else {
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) epilogue_store4<T, OutT, true>(ep, M, N, mb + i * 16, nb + j * 16, acc[i][j]);
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) epilogue_store4<T, OutT>(ep, M, N, mb + i * 16, nb + j * 16, acc[i][j]);
+  epilogue_any<T, OutT, FM, FN>(ep, M, N, mb, nb, acc);
 }
 
 // 128 x 128 with waves of 64 x 64; 128 x 64 and 64 x 64 for narrow products

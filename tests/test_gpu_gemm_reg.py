@@ -62,8 +62,8 @@ def test_register_staged_any_alignment(mdnn, layout, dt):
 
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
 def test_register_staged_epilogue_and_split(mdnn, dt):
-    """Bias, ReLU and mask stored in the storage type with an odd row stride,
-    and K split over a workspace (the last split ragged)."""
+    """Bias, ReLU, mask and beta * C stored in the storage type and in fp32 with
+    odd row strides, and K split over a workspace (the last split ragged)."""
     import torch
     for m, n, k in ((131, 77, 1001), (40, 70, 2000)):
         a, b = W.normal((m, k), 52, 1, dt, 1 / np.sqrt(k)), W.normal((k, n), 52, 2, dt)
@@ -76,3 +76,19 @@ def test_register_staged_epilogue_and_split(mdnn, dt):
         exact = np.where(decode(mk, dt) > 0, ops.bias_act(ops.gemm("NN", a64, b64), bias.astype(np.float64), "relu"), 0)
         assert lowp_close(host64(D)[:, :n], exact, dt, accum_bound(np.abs(a64) @ np.abs(b64) + np.abs(bias), k + 1))
         assert not host64(D)[:, n].any() and flag.item() == 0
+        # the kernel's own epilogue (no split), alpha and beta * C added, both output types
+        for odt in (dt, "f32"):
+            c = W.normal((m, n + 3), 52, 5, odt)
+            D = torch.zeros((m, n + 1), dtype=dev(c, odt).dtype, device="cuda")
+            mdnn.gemm(mdnn.NN, dev(a, dt), dev(b, dt), bias=dev(bias, "f32"), act=1, mask=dev(mk, dt), out=D[:, :n],
+                      alpha=0.5, beta=-2.0, Cm=dev(c, odt)[:, :n], nonfinite=flag)
+            c64 = decode(c, odt)[:, :n]
+            z = 0.5 * ops.gemm("NN", a64, b64) - 2.0 * c64 + bias
+            exact = np.where(decode(mk, dt) > 0, np.maximum(z, 0.0), 0.0)
+            bound = accum_bound(np.abs(a64) @ np.abs(b64) + 2 * np.abs(c64) + np.abs(bias), k + 3)
+            got = host64(D)
+            if odt == "f32":
+                assert np.all(np.abs(got[:, :n] - exact) <= bound)
+            else:
+                assert lowp_close(got[:, :n], exact, dt, bound)
+            assert not got[:, n].any() and flag.item() == 0
