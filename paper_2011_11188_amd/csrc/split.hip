@@ -20,42 +20,53 @@ namespace {
 
 constexpr float SHIFT_UP = 2048.0f;  // 2^11 = s / s2
 
-// rows x cols fp32 (leading dimension ldx) -> hi / lo fp16.  inv_scale = 1/s
-// (a power of two, so x * inv_scale is exact for normal results), or 1 /
-// *scale_dev when the scale was chosen on the device.
-__global__ void __launch_bounds__(256)
-split_f16_kernel(int64_t rows, int64_t cols, const float* __restrict__ x, int64_t ldx, float inv_scale,
-                 const float* __restrict__ scale_dev, uint16_t* __restrict__ hi, int64_t ldh,
-                 uint16_t* __restrict__ lo, int64_t ldl) {
-  if (scale_dev) inv_scale = 1.0f / *scale_dev;  // exact: a power of two in [2^-126, 2^113]
-  const int64_t row = blockIdx.y;
-  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < cols; c += (int64_t)gridDim.x * 256) {
-    const float v = x[row * ldx + c] * inv_scale;
-    const uint16_t h = f32_to_f16(v);
-    const float r = v - f16_to_f32(h);  // exact: v and h agree in their leading 11 bits
-    hi[row * ldh + c] = h;
-    lo[row * ldl + c] = f32_to_f16(r * SHIFT_UP);
-  }
-}
-
 // Automatic scale (the paper does not say how to pick a1): the power of two
 // s = 2^(floor(log2 max|x|) - 14), which puts max|x| / s in [2^14, 2^15),
 // inside fp16's range with its leading bits in the normal range; s = 1 when
 // max|x| is 0, Inf or NaN; s >= 2^-126.  Pass 1: max |x| as fp32 bit
 // patterns (ordered like the magnitudes; NaN above Inf), one atomic max per
 // block into a word that starts at 0.
-__global__ void __launch_bounds__(256)
-absmax_bits_kernel(int64_t rows, int64_t cols, const float* __restrict__ x, int64_t ldx, uint32_t* bits) {
-  const int64_t row = blockIdx.y;
+struct AbsmaxOp {
+  const float* x;
+  int64_t rows, cols, ldx, chunks;  // chunks: 1024-column pieces per row
+  uint32_t* bits;                   // null: not this operand
+};
+// (a few hundred blocks in all, each over many row pieces: with a block and an
+// atomic per 256 elements the serialised atomics took 200 us on 704 x 2420)
+__global__ void __launch_bounds__(256) absmax_bits_kernel(AbsmaxOp a, AbsmaxOp b) {
+  const AbsmaxOp& o = blockIdx.y == 0 ? a : b;
+  if (!o.bits) return;
   uint32_t m = 0;
-  for (int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x; c < cols; c += (int64_t)gridDim.x * 256) {
-    const uint32_t u = __float_as_uint(x[row * ldx + c]) & 0x7fffffffu;
+  auto take = [&](float f) {
+    const uint32_t u = __float_as_uint(f) & 0x7fffffffu;
     m = u > m ? u : m;
+  };
+  const int64_t n = o.rows * o.chunks;
+  for (int64_t q0 = blockIdx.x; q0 < n; q0 += 4 * (int64_t)gridDim.x) {
+    // four pieces in flight (a piece past the end repeats the first)
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    f4 t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t q = q0 + u * (int64_t)gridDim.x < n ? q0 + u * (int64_t)gridDim.x : q0;
+      const int64_t row = q / o.chunks, c = (q - row * o.chunks) * 1024 + threadIdx.x * 4;
+      const float* p = o.x + row * o.ldx;
+      t[u] = (f4){0.f, 0.f, 0.f, 0.f};
+      if (c + 4 <= o.cols) {
+        t[u] = *(const __attribute__((address_space(1))) f4*)(p + c);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (c + e < o.cols) take(p[c + e]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) take(t[u].x), take(t[u].y), take(t[u].z), take(t[u].w);
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
-    const uint32_t o = (uint32_t)__shfl_xor((int)m, off);
-    m = o > m ? o : m;
+    const uint32_t w = (uint32_t)__shfl_xor((int)m, off);
+    m = w > m ? w : m;
   }
   __shared__ uint32_t wmax[4];
   if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
@@ -63,7 +74,7 @@ absmax_bits_kernel(int64_t rows, int64_t cols, const float* __restrict__ x, int6
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) m = wmax[w] > m ? wmax[w] : m;
     m = wmax[0] > m ? wmax[0] : m;
-    if (m) atomicMax(bits, m);
+    if (m) atomicMax(o.bits, m);
   }
 }
 
@@ -74,17 +85,73 @@ __device__ float auto_scale(uint32_t bits) {
   return ldexpf(1.0f, e);
 }
 
-// Pass 2: words[0] and words[1] hold the bit maxima of A and B (or are
-// unused when a fixed scale > 0 is given); they become the scales s_a, s_b,
-// and words[2] = s_a * s_b.
-__global__ void scales_kernel(uint32_t* words, float a_fixed, float b_fixed) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const float sa = a_fixed > 0.0f ? a_fixed : auto_scale(words[0]);
-  const float sb = b_fixed > 0.0f ? b_fixed : auto_scale(words[1]);
-  float* f = (float*)words;
-  f[0] = sa;
-  f[1] = sb;
-  f[2] = sa * sb;
+// One operand: rows x cols fp32 (leading dimension ldx) -> hi / lo fp16.
+// inv_scale = 1/s (a power of two, so
+// x * inv_scale is exact for normal results), or 1 / *scale_dev, or from the
+// bit maximum in *bits when the scale is chosen on the device.
+struct SplitOp {
+  const float* x;
+  int64_t rows, cols, ldx;
+  uint16_t *hi, *lo;
+  int64_t ldh, ldl;
+  float inv_scale;
+  const float* scale_dev;
+  const uint32_t* bits;
+  int64_t chunks;  // blocks per row
+  int64_t blocks;  // blocks of this operand
+};
+constexpr int SPLIT_COLS = 1024;  // columns per block, four per thread
+
+// Blocks of both operands of a product in one launch (op b may be empty).
+// HBM-bound (4 B read, 4 B written per element): four elements per thread by
+// unaligned 16- and 8-byte accesses; element by element, one launch per
+// operand, two 2048 x 2048 operands took 21 us.  ab_scale (nullable) receives
+// the product of the two automatic or fixed scales.
+__global__ void __launch_bounds__(256) split_f16_kernel(SplitOp a, SplitOp b, float* ab_scale) {
+  for (int64_t g = blockIdx.x; g < a.blocks + b.blocks; g += gridDim.x) {
+    const bool first = g < a.blocks;
+    const SplitOp& o = first ? a : b;
+    const int64_t blk = first ? g : g - a.blocks;
+    float inv = o.inv_scale;
+    if (o.scale_dev) inv = 1.0f / *o.scale_dev;  // exact: a power of two in [2^-126, 2^113]
+    if (o.bits) inv = 1.0f / auto_scale(*o.bits);
+    if (ab_scale && g == 0 && threadIdx.x == 0)
+      *ab_scale = (a.bits ? auto_scale(*a.bits) : 1.0f / a.inv_scale) * (b.bits ? auto_scale(*b.bits) : 1.0f / b.inv_scale);
+    const int64_t row = blk / o.chunks, c = (blk - row * o.chunks) * SPLIT_COLS + threadIdx.x * 4;
+    if (c >= o.cols) continue;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    const float* p = o.x + row * o.ldx + c;
+    if (c + 4 <= o.cols) {
+      typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+      const f4 t = *(const __attribute__((address_space(1))) f4*)p;
+      v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c + e < o.cols) v[e] = p[e];
+    }
+    uint16_t h[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float w = v[e] * inv;
+      h[e] = f32_to_f16(w);
+      const float r = w - f16_to_f32(h[e]);  // exact: w and h agree in their leading 11 bits
+      l[e] = f32_to_f16(r * SHIFT_UP);
+    }
+    uint16_t* dh = o.hi + row * o.ldh + c;
+    uint16_t* dl = o.lo + row * o.ldl + c;
+    if (c + 4 <= o.cols) {
+      typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(2)));
+      *(__attribute__((address_space(1))) u2*)dh =
+          (u2){(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+      *(__attribute__((address_space(1))) u2*)dl =
+          (u2){(uint32_t)l[0] | ((uint32_t)l[1] << 16), (uint32_t)l[2] | ((uint32_t)l[3] << 16)};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (c + e < o.cols) dh[e] = h[e], dl[e] = l[e];
+    }
+  }
 }
 
 // the automatic scale of one matrix, in place (word 0 only)
@@ -101,39 +168,33 @@ bool power_of_two(float s) {
 
 size_t seg(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 
-// scale_dev: device scale (chosen on the device) or null (host `scale`)
-mdnn_status_t launch_split(int64_t rows, int64_t cols, const float* x, int64_t ldx, float scale,
-                           const float* scale_dev, void* hi, int64_t ldh, void* lo, int64_t ldl, hipStream_t st) {
-  if (rows == 0 || cols == 0) return MDNN_SUCCESS;
-  if (rows > 65535) {
-    // the grid's y extent holds the row; split tall matrices into bands
-    for (int64_t r0 = 0; r0 < rows; r0 += 65535) {
-      const int64_t nr = rows - r0 < 65535 ? rows - r0 : 65535;
-      MDNN_TRY(launch_split(nr, cols, x + r0 * ldx, ldx, scale, scale_dev, (uint16_t*)hi + r0 * ldh, ldh,
-                            (uint16_t*)lo + r0 * ldl, ldl, st));
-    }
-    return MDNN_SUCCESS;
-  }
-  int64_t bx = ceil_div(cols, 256);
-  if (bx > 1024) bx = 1024;
-  hipLaunchKernelGGL(split_f16_kernel, dim3((unsigned)bx, (unsigned)rows), dim3(256), 0, st, rows, cols, x, ldx,
-                     scale_dev ? 1.0f : 1.0f / scale, scale_dev, (uint16_t*)hi, ldh, (uint16_t*)lo, ldl);
+SplitOp split_op(int64_t rows, int64_t cols, const float* x, int64_t ldx, float scale, const float* scale_dev,
+                 const uint32_t* bits, uint16_t* hi, int64_t ldh, uint16_t* lo, int64_t ldl) {
+  SplitOp o{x, rows, cols, ldx, hi, lo, ldh, ldl, scale_dev || bits ? 1.0f : 1.0f / scale, scale_dev,
+            bits, ceil_div(cols, (int64_t)SPLIT_COLS), 0};
+  o.blocks = rows * o.chunks;
+  return o;
+}
+mdnn_status_t launch_split(const SplitOp& a, const SplitOp& b, float* ab_scale, hipStream_t st) {
+  const int64_t blocks = a.blocks + b.blocks;
+  if (blocks == 0) return MDNN_SUCCESS;
+  const unsigned grid = blocks > ((int64_t)1 << 24) ? 1u << 24 : (unsigned)blocks;  // (the kernel loops past it)
+  hipLaunchKernelGGL(split_f16_kernel, dim3(grid), dim3(256), 0, st, a, b, ab_scale);
   return check_launch("split_f16_kernel");
 }
 
-// atomic max of |x|'s bit patterns into *bits (pass 1 of the automatic scale)
-mdnn_status_t launch_absmax(int64_t rows, int64_t cols, const float* x, int64_t ldx, uint32_t* bits,
-                            hipStream_t st) {
-  if (rows == 0 || cols == 0) return MDNN_SUCCESS;
-  for (int64_t r0 = 0; r0 < rows; r0 += 65535) {
-    const int64_t nr = rows - r0 < 65535 ? rows - r0 : 65535;
-    int64_t bx = ceil_div(cols, 256);
-    if (bx > 64) bx = 64;
-    hipLaunchKernelGGL(absmax_bits_kernel, dim3((unsigned)bx, (unsigned)nr), dim3(256), 0, st, nr, cols,
-                       x + r0 * ldx, ldx, bits);
-    MDNN_TRY(check_launch("absmax_bits_kernel"));
-  }
-  return MDNN_SUCCESS;
+// atomic max of |x|'s bit patterns into the operands' words (pass 1 of the
+// automatic scale); an operand with a fixed scale has no word
+AbsmaxOp absmax_op(int64_t rows, int64_t cols, const float* x, int64_t ldx, uint32_t* bits) {
+  return AbsmaxOp{x, rows, cols, ldx, ceil_div(cols, (int64_t)1024), rows > 0 && cols > 0 ? bits : nullptr};
+}
+mdnn_status_t launch_absmax(const AbsmaxOp& a, const AbsmaxOp& b, hipStream_t st) {
+  if (!a.bits && !b.bits) return MDNN_SUCCESS;
+  const int64_t na = a.bits ? a.rows * a.chunks : 0, nb = b.bits ? b.rows * b.chunks : 0;
+  int64_t blocks = ceil_div(na > nb ? na : nb, 4);
+  if (blocks > 256) blocks = 256;
+  hipLaunchKernelGGL(absmax_bits_kernel, dim3((unsigned)blocks, b.bits ? 2 : 1), dim3(256), 0, st, a, b);
+  return check_launch("absmax_bits_kernel");
 }
 
 }  // namespace
@@ -158,18 +219,20 @@ extern "C" mdnn_status_t mdnn_split_f16(int64_t rows, int64_t cols, const float*
     return fail(MDNN_ERR_MISALIGNED, "split: misaligned base pointer");
   clear_error();
   hipStream_t st = as_stream(stream);
-  if (!automatic) return launch_split(rows, cols, x, ldx, scale, nullptr, hi, ldh, lo, ldl, st);
+  SplitOp op = split_op(rows, cols, x, ldx, scale, automatic ? scale_out : nullptr, nullptr, (uint16_t*)hi, ldh,
+                        (uint16_t*)lo, ldl);
+  if (!automatic) return launch_split(op, SplitOp{}, nullptr, st);
   uint32_t* w = (uint32_t*)scale_out;
   MDNN_TRY(fill_zero(w, 4, st));
-  MDNN_TRY(launch_absmax(rows, cols, x, ldx, w, st));
+  MDNN_TRY(launch_absmax(absmax_op(rows, cols, x, ldx, w), AbsmaxOp{}, st));
   hipLaunchKernelGGL(scale_one_kernel, dim3(1), dim3(64), 0, st, w);
   MDNN_TRY(check_launch("scale_one_kernel"));
-  return launch_split(rows, cols, x, ldx, 1.0f, scale_out, hi, ldh, lo, ldl, st);
+  return launch_split(op, SplitOp{}, nullptr, st);
 }
 
 // Workspace: [A1 | A2] (2 M K fp16), [B2 ; B1] (2 K N fp16), the fp32
-// correction product (M N), and three scale words (s_a, s_b, s_a s_b), each
-// 256-byte aligned.
+// correction product (M N), and three scale words (the bit maxima of A and
+// B, and s_a s_b), each 256-byte aligned.
 extern "C" size_t mdnn_gemm_split3_workspace(int64_t M, int64_t N, int64_t K) {
   if (M < 0 || N < 0 || K < 0) return 0;
   return seg((size_t)2 * M * K * 2) + seg((size_t)2 * K * N * 2) + seg((size_t)M * N * 4) + 256;
@@ -201,58 +264,32 @@ extern "C" mdnn_status_t mdnn_gemm_split3(mdnn_layout_t layout, int64_t M, int64
   clear_error();
   hipStream_t st = as_stream(stream);
   char* ws = (char*)workspace;
-  uint16_t* ah = (uint16_t*)ws;                                           // [A1 | A2]
-  uint16_t* bh = (uint16_t*)(ws + seg((size_t)2 * M * K * 2));            // [B2 ; B1]
-  float* dlo = (float*)(ws + seg((size_t)2 * M * K * 2) + seg((size_t)2 * K * N * 2));
-  // scales chosen on the device (a_scale or b_scale 0): the split kernels
-  // read theirs and the products' epilogues multiply alpha by s_a s_b
+  uint16_t* ah = (uint16_t*)ws;                                  // [A1 | A2]
+  uint16_t* bh = (uint16_t*)(ws + seg((size_t)2 * M * K * 2));  // [B2 ; B1]
+  float* dlo = (float*)((char*)bh + seg((size_t)2 * K * N * 2));
+  // scales chosen on the device (a_scale or b_scale 0): the split kernel
+  // derives them from the bit maxima and leaves s_a s_b, which the products'
+  // epilogues multiply into alpha
   const bool automatic = a_scale == 0.0f || b_scale == 0.0f;
-  float* scl = (float*)(ws + seg((size_t)2 * M * K * 2) + seg((size_t)2 * K * N * 2) + seg((size_t)M * N * 4));
-  const float* sa_dev = nullptr;
-  const float* sb_dev = nullptr;
-  const float* ab_dev = nullptr;
+  uint32_t* words = (uint32_t*)((char*)dlo + seg((size_t)M * N * 4));
+  const uint32_t* wa = a_scale == 0.0f ? words : nullptr;
+  const uint32_t* wb = b_scale == 0.0f ? words + 1 : nullptr;
+  const bool a_t = layout == MDNN_TN, b_t = layout != MDNN_NT;  // stored [K][M], [K][N]
+  const int64_t ar = a_t ? K : M, ac = a_t ? M : K, br = b_t ? K : N, bc = b_t ? N : K;
   if (automatic) {
-    uint32_t* w = (uint32_t*)scl;
-    MDNN_TRY(fill_zero(w, 16, st));
-    if (a_scale == 0.0f) {
-      if (layout == MDNN_TN)
-        MDNN_TRY(launch_absmax(K, M, A, lda, w, st));
-      else
-        MDNN_TRY(launch_absmax(M, K, A, lda, w, st));
-    }
-    if (b_scale == 0.0f) {
-      if (layout == MDNN_NT)
-        MDNN_TRY(launch_absmax(N, K, B, ldb, w + 1, st));
-      else
-        MDNN_TRY(launch_absmax(K, N, B, ldb, w + 1, st));
-    }
-    hipLaunchKernelGGL(scales_kernel, dim3(1), dim3(64), 0, st, w, a_scale, b_scale);
-    MDNN_TRY(check_launch("scales_kernel"));
-    sa_dev = scl;
-    sb_dev = scl + 1;
-    ab_dev = scl + 2;
+    MDNN_TRY(fill_zero(words, 16, st));
+    MDNN_TRY(launch_absmax(absmax_op(ar, ac, A, lda, (uint32_t*)wa), absmax_op(br, bc, B, ldb, (uint32_t*)wb), st));
   }
   // concatenated operands: K-contiguous ones side by side along the row,
   // MN-contiguous ones stacked by rows
-  int64_t ld_ah, ld_bh;
-  const uint16_t *a1, *b1;
-  if (layout == MDNN_TN) {  // A stored [K][M]
-    ld_ah = M;
-    MDNN_TRY(launch_split(K, M, A, lda, a_scale, sa_dev, ah, M, ah + K * M, M, st));
-  } else {  // A stored [M][K]
-    ld_ah = 2 * K;
-    MDNN_TRY(launch_split(M, K, A, lda, a_scale, sa_dev, ah, 2 * K, ah + K, 2 * K, st));
-  }
-  a1 = ah;
-  if (layout == MDNN_NT) {  // B stored [N][K]: [B2 | B1]
-    ld_bh = 2 * K;
-    MDNN_TRY(launch_split(N, K, B, ldb, b_scale, sb_dev, bh + K, 2 * K, bh, 2 * K, st));
-    b1 = bh + K;
-  } else {  // B stored [K][N]: [B2 ; B1]
-    ld_bh = N;
-    MDNN_TRY(launch_split(K, N, B, ldb, b_scale, sb_dev, bh + K * N, N, bh, N, st));
-    b1 = bh + K * N;
-  }
+  const int64_t ld_ah = a_t ? M : 2 * K, ld_bh = b_t ? N : 2 * K;
+  uint16_t* a2 = ah + (a_t ? K * M : K);
+  uint16_t* b1 = bh + (b_t ? K * N : K);
+  const uint16_t* a1 = ah;
+  float* ab_dev = automatic ? (float*)(words + 2) : nullptr;
+  MDNN_TRY(launch_split(split_op(ar, ac, A, lda, a_scale, nullptr, wa, ah, ld_ah, a2, ld_ah),
+                        split_op(br, bc, B, ldb, b_scale, nullptr, wb, b1, ld_bh, bh, ld_bh),
+                        ab_dev, st));
   const float ab = automatic ? alpha : alpha * a_scale * b_scale;
   // corrections: alpha a b 2^-11 (A1 B2 + A2 B1) + beta C
   MDNN_TRY(gemm_mixed_ws(layout, M, N, 2 * K, ab / SHIFT_UP, ah, ld_ah, bh, ld_bh, MDNN_F16, beta, C, ldc, dlo, N,

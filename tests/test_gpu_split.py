@@ -151,3 +151,33 @@ def test_gemm_split3_full_size_sampled(mdnn):
     sel = host64(got)[rows]
     assert np.all(np.abs(sel - exact) <= accum_bound(absprod, 2 * k + 2) + 2.0 ** -20 * absprod)
     assert norm_max_err(sel, exact) < 1e-6
+
+
+# Split and automatic scale at the edges of their 1024-column pieces and
+# 4-column quads, odd leading dimensions and bases; the largest magnitude in
+# the last element, and only in the other operand's range of the product.
+@pytest.mark.parametrize("shape", [(1, 1), (3, 5), (300, 1023), (7, 1025), (2, 4099), (1500, 3)])
+def test_split_and_scale_edges(mdnn, shape):
+    import torch
+    rows, cols = shape
+    x = W.normal((rows, cols + 1), 71, 1, "f32")
+    x[-1, cols - 1] = -1.5 * 2.0 ** 9
+    X = dev(x, "f32")[:, :cols]
+    hi = torch.full((rows, cols + 3), 7.0, dtype=torch.float16, device="cuda")
+    lo = torch.full((rows, cols + 1), 7.0, dtype=torch.float16, device="cuda")
+    s = torch.full((1,), 7.0, device="cuda")
+    mdnn.mdnn_split_f16(rows, cols, X, cols + 1, 0.0, s, hi, cols + 3, lo, cols + 1)
+    want_s = ops.split_scale(x[:, :cols].astype(np.float64))
+    assert s.item() == want_s
+    v = x[:, :cols] / np.float32(want_s)
+    h = v.astype(np.float16)
+    low = ((v - h.astype(np.float32)) * np.float32(2048)).astype(np.float16)
+    assert np.array_equal(hi.cpu().numpy()[:, :cols], h) and np.array_equal(lo.cpu().numpy()[:, :cols], low)
+    assert (hi[:, cols:] == 7).all() and (lo[:, cols:] == 7).all()
+    # both operands' scales in one product
+    b = W.normal((cols, 9), 71, 2, "f32", 2.0 ** -7)
+    d = mdnn.gemm_split3(mdnn.NN, X, dev(b, "f32"), a_scale=0.0, b_scale=0.0)
+    want = x[:, :cols].astype(np.float64) @ b.astype(np.float64)
+    size = np.abs(x[:, :cols]).astype(np.float64) @ np.abs(b).astype(np.float64)
+    # two-term splits (2^-21 per product) and three fp32 sums
+    assert np.all(np.abs(host64(d) - want) <= size * (2.0 ** -20 + 3 * (cols + 2) * 2.0 ** -24) + 1e-30)
