@@ -5,6 +5,7 @@
 // No im2col buffer is materialised: the operand sources compute addresses.
 #include <mutex>
 
+#include "conv_gather.h"
 #include "conv_halo.h"
 #include "conv_pipe.h"
 #include "conv_reg.h"
@@ -137,8 +138,9 @@ extern "C" mdnn_status_t mdnn_conv2d_fwd(const mdnn_conv_shape_t* shape, const v
   clear_error();
   hipStream_t st = as_stream(stream);
   if (pipe_allowed()) {
-    if (conv_small_fwd_ok(g)) return conv_small_fwd(g, x, w, ep, io_type, y_type, st);
     bool done = false;
+    MDNN_TRY(conv_gather_fwd(g, x, w, ep, io_type, y_type, st, &done));
+    if (done) return MDNN_SUCCESS;
     if (halo_allowed()) MDNN_TRY(conv_halo(g, false, x, w, ep, io_type, y_type, st, &done));
     if (done) return MDNN_SUCCESS;
     MDNN_TRY(conv_pipe_fwd(g, x, w, ep, io_type, y_type, st, &done));

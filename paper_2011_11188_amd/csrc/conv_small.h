@@ -9,12 +9,6 @@ namespace mdnn {
 // Validates a convolution shape (sizes, output not empty, ranges) into g.
 mdnn_status_t check_conv_shape(const mdnn_conv_shape_t* s, ConvGeom& g);
 
-// Forward with K = r*s*c_in <= 64 and c_out <= 256: any storage type, any
-// epilogue (bias, ReLU, output type).
-bool conv_small_fwd_ok(const ConvGeom& g);
-mdnn_status_t conv_small_fwd(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, mdnn_dtype_t io,
-                             mdnn_dtype_t out, hipStream_t st);
-
 // Filter gradient with r*s*c_in <= 64 and c_out * r*s*c_in <= 1024: number
 // of pixel blocks (the partials it writes:
 // blocks * c_out * r*s*c_in floats), or 0 when the shape does not qualify.

@@ -1,18 +1,10 @@
-// Convolutions with a tiny reduction (section 2.1's convolution layers; the
-// first layer of an image network, e.g. one input channel and a 5x5 filter):
-// the GEMM engine would spend almost all of a tile on padding, so these run
-// as direct kernels on the vector ALUs, fp32 accumulation.
-//
-//   forward (K = r*s*c_in <= 64): with c_out <= 32 a thread owns one output
-//     pixel (its im2col row gathered once into LDS, the filter staged once per
-//     256 pixels, all channels from broadcast filter reads); wider outputs:
-//     a block stages the im2col rows of 64 output pixels and the whole filter
-//     in LDS, and each thread produces four consecutive output channels of
-//     one pixel.  Both end in the shared epilogue.
-//   backward filter (c_out * r*s*c_in <= 1024 outputs, r*s*c_in <= 64): each
-//     block accumulates every filter element over its chunk of output pixels
-//     into fp32 partials, which the split reduction then sums in a fixed
-//     order (deterministic).
+// Filter gradients of convolutions with a tiny reduction (section 2.1's
+// convolution layers; the first layer of an image network, e.g. one input
+// channel and a 5x5 filter; c_out * r*s*c_in <= 1024 outputs, r*s*c_in <=
+// 64): the GEMM engine would spend almost all of a tile on padding.  Each
+// block accumulates every filter element over its chunk of output pixels
+// into fp32 partials, which the split reduction then sums in a fixed order
+// (deterministic).  (The forward passes: conv_gather.hip.)
 #include "conv_small.h"
 
 namespace mdnn {
@@ -68,118 +60,7 @@ __host__ __device__ constexpr int odd_stride(int cols) { return cols | 1; }
 // channels are one 16-byte LDS read.
 __host__ __device__ constexpr int quad_pad(int n) { return (n + 3) & ~3; }
 
-template <class T, class OutT>
-__global__ void __launch_bounds__(256)
-conv_small_fwd_kernel(const typename T::storage* __restrict__ x, const typename T::storage* __restrict__ w,
-                      ConvGeom g, int64_t M, Epilogue ep) {
-  extern __shared__ float smem[];
-  const int K = g.r * g.s * g.c, N = g.k, KS = odd_stride(K), NP = quad_pad(N);
-  float* xs = smem;            // [TP][KS] im2col rows
-  float* wt = smem + TP * KS;  // [K][NP] filter, transposed (zero beyond N)
-  const int tid = threadIdx.x;
-  stage<T>(w, K * NP, [=](int e) -> int64_t { const int kk = e / NP, n = e - kk * NP; return n < N ? (int64_t)n * K + kk : -1; },
-           [](int e) { return e; }, wt);
-  const int64_t m0 = (int64_t)blockIdx.x * TP;
-  stage<T>(
-      x, TP * K, [=](int e) -> int64_t { const int p = e / K; return m0 + p < M ? patch_off(g, m0 + p, e - p * K) : -1; },
-      [=](int e) { return (e / K) * KS + e % K; }, xs);
-  __syncthreads();
-  // thread task: pixel p, output channels n4 .. n4+3 (one 16-byte read of the
-  // filter and one broadcast read of the patch per four FMAs)
-  const int groups = NP / 4;
-  for (int q = tid; q < TP * groups; q += 256) {
-    const int p = q / groups, n4 = (q - p * groups) * 4;
-    float4_t acc = {0.f, 0.f, 0.f, 0.f};
-    const float* xr = xs + p * KS;
-    for (int kk = 0; kk < K; ++kk) {
-      const float a = xr[kk];
-      const float4 b = *(const float4*)(wt + kk * NP + n4);
-      acc[0] = fmaf(a, b.x, acc[0]);
-      acc[1] = fmaf(a, b.y, acc[1]);
-      acc[2] = fmaf(a, b.z, acc[2]);
-      acc[3] = fmaf(a, b.w, acc[3]);
-    }
-    epilogue_store4<T, OutT>(ep, M, N, m0 + p, n4, acc);
-  }
-}
-
-// Narrow outputs (c_out <= 32): one output pixel per thread.  The thread
-// decomposes its pixel once and gathers its own im2col row (taps walked with
-// counters, eight loads in flight) into LDS, the block stages the filter
-// once for 256 pixels, and the thread then produces all c_out channels from
-// its row and broadcast reads of the filter.
-constexpr int PX = 256;         // output pixels per block (one per thread)
-constexpr int PX_QUADS = 8;     // c_out <= 32
-
-template <class T, class OutT>
-__global__ void __launch_bounds__(256)
-conv_small_fwd_px_kernel(const typename T::storage* __restrict__ x, const typename T::storage* __restrict__ w,
-                         ConvGeom g, int64_t M, Epilogue ep) {
-  extern __shared__ float smem[];
-  const int K = g.r * g.s * g.c, N = g.k, KS = odd_stride(K), NP = quad_pad(N), nq = NP / 4;
-  float* xs = smem;            // [PX][KS] im2col rows
-  float* wt = smem + PX * KS;  // [K][NP] filter, transposed (zero beyond N)
-  const int tid = threadIdx.x;
-  stage<T>(w, K * NP, [=](int e) -> int64_t { const int kk = e / NP, n = e - kk * NP; return n < N ? (int64_t)n * K + kk : -1; },
-           [](int e) { return e; }, wt);
-  const int64_t m = (int64_t)blockIdx.x * PX + tid;
-  float* row = xs + tid * KS;
-  if (m < M) {
-    const int mi = (int)m, hw = g.ho * g.wo;  // pixel counts below 2^31 on this path
-    const int n = mi / hw, rem = mi - n * hw, i = rem / g.wo, j = rem - i * g.wo;
-    const typename T::storage* xn = x + (int64_t)n * g.h * g.w * g.c;
-    int tr = 0, ts = 0, ch = 0;  // tap row, tap column, channel of element kk
-    for (int kb = 0; kb < K; kb += 8) {
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int y = i + tr - g.pad, xx = j + ts - g.pad;
-        const bool ok = kb + u < K && (unsigned)y < (unsigned)g.h && (unsigned)xx < (unsigned)g.w;
-        const float val = to_f<T>(xn[ok ? ((int64_t)y * g.w + xx) * g.c + ch : 0]);
-        v[u] = ok ? val : 0.0f;
-        if (++ch == g.c) {
-          ch = 0;
-          if (++ts == g.s) {
-            ts = 0;
-            ++tr;
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (kb + u < K) row[kb + u] = v[u];
-    }
-  }
-  __syncthreads();
-  if (m >= M) return;
-  float4_t acc[PX_QUADS];
-#pragma unroll
-  for (int q = 0; q < PX_QUADS; ++q) acc[q] = (float4_t){0.f, 0.f, 0.f, 0.f};
-  for (int kk = 0; kk < K; ++kk) {
-    const float a = row[kk];
-    const float* wk = wt + kk * NP;
-#pragma unroll
-    for (int q = 0; q < PX_QUADS; ++q) {
-      if (q < nq) {
-        const float4 b = *(const float4*)(wk + 4 * q);
-        acc[q][0] = fmaf(a, b.x, acc[q][0]);
-        acc[q][1] = fmaf(a, b.y, acc[q][1]);
-        acc[q][2] = fmaf(a, b.z, acc[q][2]);
-        acc[q][3] = fmaf(a, b.w, acc[q][3]);
-      }
-    }
-  }
-  const bool full = full_tile_epilogue(ep, 4 * nq <= N, N);
-#pragma unroll
-  for (int q = 0; q < PX_QUADS; ++q) {
-    if (q < nq) {
-      if (full)
-        epilogue_store4<T, OutT, true>(ep, M, N, m, 4 * q, acc[q]);
-      else
-        epilogue_store4<T, OutT>(ep, M, N, m, 4 * q, acc[q]);
-    }
-  }
-}
+constexpr int PX = 256;  // output pixels per block of the per-pixel filter gradient (one per thread)
 
 // partial[b][k][kk] over the pixels of block b (pixels_per_block of them).
 // Thread task: output channels k4 .. k4+3 of filter column kk; per pixel one
@@ -317,10 +198,8 @@ conv_small_filter_px_kernel(const typename T::storage* __restrict__ x, const typ
 }
 
 // ---------------------------------------------------------------------------
-// 16-bit data with K = r*s*c_in <= 32: the whole reduction of a forward
-// output is one 32-deep MFMA step, and the filter gradient is a product of
-// depth n*ho*wo with a 32 x 32 (or smaller) result; both run on the matrix
-// cores.  Fragments are gathered straight from global memory (x is small
+// 16-bit data with K = r*s*c_in <= 32: the filter gradient is a product of
+// depth n*ho*wo with a 32 x 32 (or smaller) result on the matrix cores.  Fragments are gathered straight from global memory (x is small
 // and stays in the caches): lane l owns row l % 16 of a 16 x 32 operand
 // fragment and the eight consecutive reduction indices 8 (l / 16) .. + 7,
 // zero past the reduction, in the padding or past the last pixel.
@@ -352,54 +231,6 @@ __device__ __forceinline__ uint4 im2col8(const typename T::storage* __restrict__
     }
   }
   return pack8(v);
-}
-
-// y[m][n] = epi(sum_kk im2col[m][kk] w[n][kk]): a wave loads the filter's
-// fragments once (all output channels, up to 64, 16 per MFMA), then handles
-// MF_Q blocks of 16 output pixels with every block's gathers in flight
-// together before any of its products.
-constexpr int MF_NB = 4;
-constexpr int MF_Q = 4;
-template <class T, class OutT>
-__global__ void __launch_bounds__(256)
-conv_small_fwd_mfma_kernel(const typename T::storage* __restrict__ x, const typename T::storage* __restrict__ w,
-                           ConvGeom g, int64_t M, Epilogue ep) {
-  const int lane = threadIdx.x & 63;
-  const int K = g.r * g.s * g.c, N = g.k, nb_n = (N + 15) / 16;
-  const int64_t pb0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * MF_Q;
-  if (pb0 * 16 >= M) return;
-  const int kk0 = 8 * (lane >> 4);
-  uint4 wf[MF_NB];
-#pragma unroll
-  for (int nb = 0; nb < MF_NB; ++nb) {
-    const int n = nb * 16 + (lane & 15);
-    uint16_t v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const bool ok = nb < nb_n && n < N && kk0 + e < K;
-      const uint16_t val = w[ok ? (int64_t)n * K + kk0 + e : 0];
-      v[e] = ok ? val : (uint16_t)0;
-    }
-    wf[nb] = pack8(v);
-  }
-  uint4 a[MF_Q];
-#pragma unroll
-  for (int q = 0; q < MF_Q; ++q) {
-    const int64_t m = (pb0 + q) * 16 + (lane & 15);
-    a[q] = im2col8<T>(x, g, (int)(m < M ? m : 0), m < M, kk0, K);
-  }
-  const int64_t nrow = 4 * (lane >> 4);
-#pragma unroll
-  for (int q = 0; q < MF_Q; ++q) {
-    const int64_t mrow = (pb0 + q) * 16 + (lane & 15);
-#pragma unroll
-    for (int nb = 0; nb < MF_NB; ++nb) {
-      if (nb < nb_n) {
-        const float4_t acc = Mfma<T>::run(wf[nb], a[q], (float4_t){0.f, 0.f, 0.f, 0.f});
-        epilogue_store4<T, OutT>(ep, M, N, mrow, nb * 16 + nrow, acc);
-      }
-    }
-  }
 }
 
 // partial[b][k][kk] = sum over block b's pixels of dy[p][k] * im2col[p][kk]
@@ -507,15 +338,6 @@ bool mfma_small(const ConvGeom& g, mdnn_dtype_t io) { return io != MDNN_F32 && g
 constexpr int64_t FILTER_PIXELS = 128;  // pixels per block of the filter gradient (enough blocks to hide the staging latency)
 constexpr size_t LDS_LIMIT = 65536;      // dynamic LDS bytes per block
 
-size_t fwd_lds(const ConvGeom& g) {
-  const int K = g.r * g.s * g.c;
-  return ((size_t)TP * odd_stride(K) + (size_t)K * quad_pad(g.k)) * sizeof(float);
-}
-size_t fwd_px_lds(const ConvGeom& g) {
-  const int K = g.r * g.s * g.c;
-  return ((size_t)PX * odd_stride(K) + (size_t)K * quad_pad(g.k)) * sizeof(float);
-}
-bool fwd_px_ok(const ConvGeom& g) { return quad_pad(g.k) <= 4 * PX_QUADS && fwd_px_lds(g) <= LDS_LIMIT; }
 size_t filter_lds(const ConvGeom& g) {
   return (size_t)TP * (odd_stride(g.r * g.s * g.c) + quad_pad(g.k)) * sizeof(float);
 }
@@ -527,60 +349,6 @@ bool filter_px_ok(const ConvGeom& g) { return filter_px_lds(g) <= LDS_LIMIT; }
 }  // namespace
 
 static bool pixels_fit(const ConvGeom& g) { return (int64_t)g.n * g.ho * g.wo < ((int64_t)1 << 31); }
-
-bool conv_small_fwd_ok(const ConvGeom& g) {
-  return g.r * g.s * g.c <= 64 && g.k <= 256 && fwd_lds(g) <= LDS_LIMIT && pixels_fit(g);
-}
-
-template <class T, class OutT>
-static void small_fwd_launch(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, int64_t M,
-                             bool px, hipStream_t st) {
-  typedef typename T::storage S;
-  if (px)
-    hipLaunchKernelGGL((conv_small_fwd_px_kernel<T, OutT>), dim3((unsigned)ceil_div(M, PX)), dim3(256),
-                       fwd_px_lds(g), st, (const S*)x, (const S*)w, g, M, ep);
-  else
-    hipLaunchKernelGGL((conv_small_fwd_kernel<T, OutT>), dim3((unsigned)ceil_div(M, TP)), dim3(256), fwd_lds(g),
-                       st, (const S*)x, (const S*)w, g, M, ep);
-}
-
-template <class T, class OutT>
-static void small_fwd_mfma_launch(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, int64_t M,
-                                  hipStream_t st) {
-  typedef typename T::storage S;
-  hipLaunchKernelGGL((conv_small_fwd_mfma_kernel<T, OutT>), dim3((unsigned)ceil_div(M, 64 * MF_Q)), dim3(256), 0, st,
-                     (const S*)x, (const S*)w, g, M, ep);
-}
-
-mdnn_status_t conv_small_fwd(const ConvGeom& g, const void* x, const void* w, const Epilogue& ep, mdnn_dtype_t io,
-                             mdnn_dtype_t out, hipStream_t st) {
-  const int64_t M = (int64_t)g.n * g.ho * g.wo;
-  if (M == 0) return MDNN_SUCCESS;
-  if (ceil_div(M, TP) > 0x7fffffffLL) return fail(MDNN_ERR_SHAPE, "conv: too many output pixels");
-  if (mfma_small(g, io) && g.k <= 16 * MF_NB) {
-    // one 32-deep matrix-core step per 16 pixels x 16 channels
-    if (io == MDNN_F16) {
-      if (out == MDNN_F32) small_fwd_mfma_launch<F16, F32>(g, x, w, ep, M, st);
-      else small_fwd_mfma_launch<F16, F16>(g, x, w, ep, M, st);
-    } else {
-      if (out == MDNN_F32) small_fwd_mfma_launch<BF16, F32>(g, x, w, ep, M, st);
-      else small_fwd_mfma_launch<BF16, BF16>(g, x, w, ep, M, st);
-    }
-    return check_launch("conv_small_fwd_mfma_kernel");
-  }
-  // one pixel per thread when c_out fits its registers
-  const bool px = fwd_px_ok(g);
-  if (io == MDNN_F16) {
-    if (out == MDNN_F32) small_fwd_launch<F16, F32>(g, x, w, ep, M, px, st);
-    else small_fwd_launch<F16, F16>(g, x, w, ep, M, px, st);
-  } else if (io == MDNN_BF16) {
-    if (out == MDNN_F32) small_fwd_launch<BF16, F32>(g, x, w, ep, M, px, st);
-    else small_fwd_launch<BF16, BF16>(g, x, w, ep, M, px, st);
-  } else {
-    small_fwd_launch<F32, F32>(g, x, w, ep, M, px, st);
-  }
-  return check_launch("conv_small_fwd_kernel");
-}
 
 // the matrix-core filter gradient: 16-bit data, K <= 32, c_out <= 32
 static bool filter_mfma_ok(const ConvGeom& g, mdnn_dtype_t io) { return mfma_small(g, io) && g.k <= 32; }
