@@ -4,8 +4,9 @@
 // im2col buffer exists.
 //
 // Tiles:
-//   forward / backward data: 256 x 64 when N <= 64 (8 waves of 64 x 32);
-//   else 128 x 128 (8 waves of 64 x 32), or 64 x 128 (4 waves of 32 x 64)
+//   forward / backward data: 256 x 64 when N <= 64 (8 waves of 64 x 32; 128 x
+//   64 where those would leave CUs idle) or the last 128 columns would be half
+//   empty; else 128 x 128 (8 waves of 64 x 32), or 64 x 128 (4 waves of 32 x 64)
 //   when 128 x 128 tiles would leave CUs idle (3x3, 256 -> 256 at 8x8,
 //   batch 128: 128 tiles; forward 21.1 -> 16.3 us, backward data 23.0 ->
 //   18.8 us); 2 stages.
@@ -25,6 +26,7 @@ namespace mdnn {
 namespace {
 
 typedef lds::Tile<256, 64, 4, 2, 4> TileTall;
+typedef lds::Tile<128, 64, 2, 2, 2> TileLow;
 typedef lds::Tile<128, 128, 2, 4, 4> TileSquare;
 typedef lds::Tile<64, 128, 2, 2, 4> TileFlat;
 // backward filter
@@ -36,6 +38,10 @@ typedef lds::Tile<64, 64, 2, 2, 4> TileFiltS;
 bool narrow_tiles(int64_t M, int64_t N) {
   return N <= 64 || ((N - 1) % 128 < 64 && ceil_div(M, 256) * ceil_div(N, 64) >= 256);
 }
+// narrow outputs whose 256-row tiles leave CUs idle: 128 x 64 tiles (64 ->
+// 64 channels, 3x3, 64 x 7 x 7 fp16: forward 10.8 -> 8.6, backward data 12.9
+// -> 9.6 us; 40 -> 64, 32 x 28 x 28 bf16 backward data 14.2 -> 11.9 us)
+bool low_tiles(int64_t M, int64_t N) { return N <= 64 && ceil_div(M, 256) < 256; }
 // 128 x 128 tiles fill fewer than 256 workgroups: the 64 x 128 tile instead
 bool flat_tiles(int64_t M, int64_t N) { return ceil_div(M, 128) * ceil_div(N, 128) < 256; }
 constexpr int FILTER_STAGES = 3;
@@ -56,12 +62,14 @@ mdnn_status_t rows_dispatch(const lds::ConvRowsArgs& a, const void* w, int32_t l
                             int64_t N, int64_t K, const Epilogue& ep, hipStream_t st) {
   if constexpr (!BWD) {
     const lds::MatArgs b{w, ldw, N};
+    if (low_tiles(M, N)) return run_rows<T, OutT, TileLow, lds::MatLoader<true, 64, TileLow::LB>>(a, b, M, N, K, ep, st);
     if (N <= 64) return run_rows<T, OutT, TileTall, lds::MatLoader<true, 64, TileTall::LB>>(a, b, M, N, K, ep, st);
     if (flat_tiles(M, N))
       return run_rows<T, OutT, TileFlat, lds::MatLoader<true, 128, TileFlat::LB>>(a, b, M, N, K, ep, st);
     return run_rows<T, OutT, TileSquare, lds::MatLoader<true, 128, TileSquare::LB>>(a, b, M, N, K, ep, st);
   } else {
     const lds::TapWeightArgs b{w, g.k, g.r * g.s, g.c};
+    if (low_tiles(M, N)) return run_rows<T, OutT, TileLow, lds::TapWeightLoader<64, TileLow::LB>>(a, b, M, N, K, ep, st);
     if (N <= 64) return run_rows<T, OutT, TileTall, lds::TapWeightLoader<64, TileTall::LB>>(a, b, M, N, K, ep, st);
     if (flat_tiles(M, N))
       return run_rows<T, OutT, TileFlat, lds::TapWeightLoader<128, TileFlat::LB>>(a, b, M, N, K, ep, st);
@@ -104,6 +112,7 @@ mdnn_status_t run_runs8(const lds::ConvRunsArgs& a, const ConvGeom& g, const voi
 template <class T, class OutT, bool BWD>
 mdnn_status_t runs8_dispatch(const lds::ConvRunsArgs& a, const ConvGeom& g, const void* w, int64_t M, int64_t N,
                              int64_t K, const Epilogue& ep, hipStream_t st) {
+  if (low_tiles(M, N)) return run_runs8<T, OutT, TileLow, BWD>(a, g, w, M, N, K, ep, st);
   if (narrow_tiles(M, N)) return run_runs8<T, OutT, TileTall, BWD>(a, g, w, M, N, K, ep, st);
   if (flat_tiles(M, N)) return run_runs8<T, OutT, TileFlat, BWD>(a, g, w, M, N, K, ep, st);
   return run_runs8<T, OutT, TileSquare, BWD>(a, g, w, M, N, K, ep, st);
