@@ -369,16 +369,30 @@ softmax_xent_kernel(int64_t B, int64_t C, const float* z, int64_t ldl, const int
   const float inv_b = 1.0f / (float)B;
   const int64_t r0 = (int64_t)blockIdx.x * rows, r1 = r0 + rows < B ? r0 + rows : B;
   const bool alone = gridDim.x == 1;
+  const int base = threadIdx.x & 63 & ~(G - 1);  // this group's first lane
   float acc = 0.0f;  // this group's rows, in order
-  for (int64_t r = r0 + grp; r < r1; r += ng) {
+  float v[V];
+  int32_t lab = 0;
+  // The next row's logits are on their way while this one is worked on: one
+  // block walks many rows, and a row is little more than latency.
+  const auto load = [&](int64_t r, float (&d)[V], int32_t& dl) {
     const float* zr = z + r * ldl;
-    const int32_t lab = labels[r];
-    const bool ok = lab >= 0 && lab < C;
-    float v[V];
-    float m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < V; ++i) v[i] = l + i * G < C ? zr[l + i * G] : -INFINITY;
-    const float zl = zr[ok ? lab : 0];
+    for (int i = 0; i < V; ++i) d[i] = l + i * G < C ? zr[l + i * G] : -INFINITY;
+    dl = labels[r];
+  };
+  if (r0 + grp < r1) load(r0 + grp, v, lab);
+  for (int64_t r = r0 + grp; r < r1; r += ng) {
+    float vn[V] = {};
+    int32_t labn = 0;
+    if (r + ng < r1) load(r + ng, vn, labn);
+    const bool ok = lab >= 0 && lab < C;
+    float m = -INFINITY;
+    float zl = v[0];
+#pragma unroll
+    for (int i = 1; i < V; ++i)
+      if (l + i * G == lab) zl = v[i];
+    zl = __shfl(zl, base + (ok ? lab % G : 0), 64);
 #pragma unroll
     for (int i = 0; i < V; ++i) m = fmaxf(m, v[i]);
 #pragma unroll
@@ -399,6 +413,9 @@ softmax_xent_kernel(int64_t B, int64_t C, const float* z, int64_t ldl, const int
     }
     acc += ok ? (lse - zl) : NAN;
     if (r == r0 && l == 0) lse0 = lse;
+#pragma unroll
+    for (int i = 0; i < V; ++i) v[i] = vn[i];
+    lab = labn;
   }
   if (l == 0) gsum[grp] = acc;
   __syncthreads();
@@ -1006,10 +1023,13 @@ mdnn_status_t launch_xent_rows(int64_t B, int64_t C, const float* logits, int64_
 
 // Rows spread over the chip: four row groups per block, at most 4096 blocks
 // (the finish kernel then reads at most four stashes per thread).  One block
-// does it all, in one launch, for up to 32 rows or 128 64-column pieces of
-// rows (eight per wave: eager calls 7.3-9 us, where two launches take the
-// host 10.3 us), and where the gradients overlap the logits (the finish
-// kernel reads logits again).
+// does it all, in one launch, where the gradients overlap the logits (the
+// finish kernel reads logits again), and for the few rows that its sixteen
+// waves walk in less time than two launches take the host (9.2-10.4 us):
+// up to 128 rows of 64 classes (8.4 us), 80 of 256 (8.5-9.6), 48 of 512
+// (8.8-9.7) and 24 above (8.9 at 1000).  96 x 128 takes one block 9.8, 64 x 257
+// 10.9, 32 x 1024 11.4.  Unfilled registers of a row cost as much as filled
+// ones (128 x 40: 11.5 us with four, 8.3 with one), hence four widths.
 template <class OutT>
 static mdnn_status_t launch_xent(int64_t B, int64_t C, const float* z, int64_t ldl, const int32_t* labels,
                                  const float* scale, float* loss_out, void* dlogits, int64_t ldd, hipStream_t st) {
@@ -1017,7 +1037,8 @@ static mdnn_status_t launch_xent(int64_t B, int64_t C, const float* z, int64_t l
   S* dz = (S*)dlogits;
   const uintptr_t z0 = (uintptr_t)z, z1 = (uintptr_t)(z + (B - 1) * ldl + C);
   const uintptr_t d0 = (uintptr_t)dz, d1 = (uintptr_t)(dz + (B - 1) * ldd + C);
-  const bool one = B <= 32 || B * ceil_div(C, 64) <= 128 || (z0 < d1 && d0 < z1);
+  const int64_t walk = C <= 64 ? 128 : C <= 256 ? 80 : C <= 512 ? 48 : 24;
+  const bool one = B <= walk || (z0 < d1 && d0 < z1);
   const bool few = C <= SMALL_C;
   const int per = few ? 32 : 4;  // rows a block of 256 threads has in flight
   int64_t nblocks = 1, rows = B;
@@ -1026,15 +1047,14 @@ static mdnn_status_t launch_xent(int64_t B, int64_t C, const float* z, int64_t l
     nblocks = ceil_div(B, rows);
   }
   const dim3 grid((unsigned)nblocks), blk(one ? LOSS_THREADS : 256);
-  if (few)
-    hipLaunchKernelGGL((softmax_xent_kernel<OutT, 8, 4>), grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out, dz,
-                       ldd, rows);
-  else if (C <= 256)
-    hipLaunchKernelGGL((softmax_xent_kernel<OutT, 64, 4>), grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out, dz,
-                       ldd, rows);
-  else
-    hipLaunchKernelGGL((softmax_xent_kernel<OutT, 64, 16>), grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out,
-                       dz, ldd, rows);
+  const auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, blk, 0, st, B, C, z, ldl, labels, scale, loss_out, dz, ldd, rows);
+  };
+  if (few) run(softmax_xent_kernel<OutT, 8, 4>);
+  else if (C <= 64) run(softmax_xent_kernel<OutT, 64, 1>);
+  else if (C <= 256) run(softmax_xent_kernel<OutT, 64, 4>);
+  else if (C <= 512) run(softmax_xent_kernel<OutT, 64, 8>);
+  else run(softmax_xent_kernel<OutT, 64, 16>);
   MDNN_TRY(check_launch("softmax_xent_kernel"));
   if (nblocks == 1) return MDNN_SUCCESS;
   hipLaunchKernelGGL((softmax_xent_finish_kernel<OutT>), dim3(1), dim3(LOSS_THREADS), 0, st, B, nblocks, rows, z, ldl,

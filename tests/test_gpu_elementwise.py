@@ -212,11 +212,13 @@ def test_softmax_xent(mdnn, dt, shape):
     assert norm_max_err(host64(dz), dzw) <= (1e-6 if dt == "f32" else 2.0 ** -8)
 
 
-# Rows over several blocks (more than 32, or more than 1024 rows of at most 32
-# classes): one row past a block, 4 classes (16-bit: the whole row is the
-# block's stash), either side of 32 and 256 classes, several rows per group
+# Rows over several blocks, or walked by one: one row past a block, 4 classes
+# (16-bit: the whole row is the block's stash), either side of 32, 64, 256 and
+# 512 classes and of the rows one block walks there, several rows per group
 # (more than 16384 rows), a row stride that leaves rows 2-byte aligned.
-@pytest.mark.parametrize("shape", [(33, 33), (1025, 4), (1057, 32), (130, 256), (131, 257), (64, 1024), (16390, 40)])
+@pytest.mark.parametrize("shape", [(33, 33), (1025, 4), (1057, 32), (130, 256), (131, 257), (64, 1024), (16390, 40),
+                                   (128, 64), (129, 64), (80, 65), (81, 256), (48, 257), (49, 512), (24, 513),
+                                   (25, 1024)])
 @pytest.mark.parametrize("dt", ["f32", "f16", "bf16"])
 def test_softmax_xent_rows_over_blocks(mdnn, dt, shape):
     import torch
