@@ -322,7 +322,7 @@ constexpr int LOSS_THREADS = 1024;
 // added in a fixed order.  HBM-bound (4 + es bytes per logit): one block
 // walking all rows (the loss sum has no scratch memory to be spread over)
 // took 3752 us for 4096 x 1000 fp16 gradients, 24.6 MB; spread over the chip
-// it takes 15.4 us, the second launch included.
+// it takes 15.4-16.0 us, the second launch included.
 //
 // With more than one block a block leaves its loss sum, and the lse of its
 // first row, in that row's first stored gradients (8 bytes), and
