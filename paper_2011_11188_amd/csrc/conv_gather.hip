@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(256, 2) conv_gather_kernel(GatherArgs a, Epilo
     }
 #pragma unroll
   for (int s = 0; s < KS; ++s)
-    if (row[s] >= a.rows) row[s] = 1 << 24;  // past the filter: outside every image
+    if (row[s] >= a.rows) row[s] = 1 << 30;  // past the filter: outside every image
 
   const int groups = (a.M + 15) / 16, stride = (int)gridDim.x * 4;
   auto load = [&](int g, Group<KS>& G) {

@@ -277,7 +277,7 @@ struct RunRowsLoader {
     for (int q = 0; q < P; ++q) {
       where(t, q, r[q], e[q]);
       rel[q] = r[q] * wsC + e[q];
-      if (r[q] >= rows) r[q] = 1 << 24;  // past the filter: outside every image
+      if (r[q] >= rows) r[q] = 1 << 30;  // past the filter: outside every image
     }
     bool any = false;
     f.keep = 0;

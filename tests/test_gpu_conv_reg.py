@@ -89,3 +89,19 @@ def _check(mdnn, shape, dt, gap):
             ("db", db, val["dy"].sum((0, 1, 2)), mag["dy"].sum((0, 1, 2)), n * ho * wo)):
         err = np.abs(host64(got) - want)
         assert np.all(err <= accum_bound(size, k + 1)), (name, shape, dt, float(np.nanmax(err)), bool(np.isnan(err).any()))
+
+
+def test_conv_tall_image_reads_nothing_past_the_filter(mdnn):
+    """An image of more than 2^24 rows: the K steps end in rows past the
+    filter, which must stay outside the image for every output (an Inf four
+    rows below an output, one row past the filter, must not reach it)."""
+    import torch
+    h, ci, r, pad, row = (1 << 24) + 4096, 5, 7, 3, 10
+    x = torch.zeros((1, h, 1, ci), dtype=torch.float16, device="cuda")
+    x[0, row] = float("inf")
+    wt = torch.ones((1, r, r, ci), dtype=torch.float16, device="cuda")
+    y = torch.full((1, h, 1, 1), float("nan"), device="cuda")
+    mdnn.mdnn_conv2d_fwd(mdnn.ConvShape(1, h, 1, ci, 1, r, r, pad), x, wt, DT["f16"], None, 0, y, DT["f32"])
+    want = torch.zeros_like(y)
+    want[0, row - pad:row + pad + 1] = float("inf")
+    assert torch.equal(y, want)
