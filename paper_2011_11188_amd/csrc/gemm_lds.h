@@ -82,7 +82,7 @@ struct Tile {
 
 // Block swizzle of an MN-contiguous tile of width W elements (see above).
 template <int W>
-__device__ __forceinline__ int mn_swz(int k) {
+__host__ __device__ __forceinline__ int mn_swz(int k) {
   if constexpr (W >= 128)
     return (k & 3) | (((k >> 3) & 1) << 2);
   else
@@ -97,7 +97,7 @@ struct LoadPos {
   int r, c;
 };
 template <bool KC, int W, int L>
-__device__ __forceinline__ LoadPos load_pos(int wave, int lane, int i) {
+__host__ __device__ __forceinline__ LoadPos load_pos(int wave, int lane, int i) {
   const int blk = wave * L + i;
   if constexpr (KC) {
     const int r = blk * 8 + (lane >> 3);

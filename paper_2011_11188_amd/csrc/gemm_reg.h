@@ -109,7 +109,7 @@ __device__ __forceinline__ uint4 keep_chunk(uint4 v, uint32_t keep, int i) {
 
 // What load i of this lane fetches (as lds::load_pos, for either element size).
 template <class T, bool KC, int W, int L>
-__device__ __forceinline__ LoadPos load_pos(int wave, int lane, int i) {
+__host__ __device__ __forceinline__ LoadPos load_pos(int wave, int lane, int i) {
   if constexpr (sizeof(typename T::storage) == 2) {
     return lds::load_pos<KC, W, L>(wave, lane, i);
   } else if constexpr (KC) {
@@ -132,7 +132,9 @@ struct MatArgs {
 
 // Plain matrix, K-contiguous ([MN][ld >= K]) or MN-contiguous ([K][ld >= MN]).
 // K >= E, and MN >= E when MN-contiguous; byte offsets within the operand
-// (K-contiguous) or within one step (MN-contiguous) below 2^32.
+// (K-contiguous: and one whole step past the start of its last row, where a
+// shorter K's last chunks lie before they are moved back) or within one step
+// (MN-contiguous) below 2^32.
 template <class T, bool KC_, int W, int L>
 struct MatLoader {
   static constexpr bool KC = KC_;
@@ -145,7 +147,8 @@ struct MatLoader {
   uint32_t off[L];
   int32_t kpos[L];  // KC: k of the chunk within a step; else its k-row
 
-  __device__ __forceinline__ void init(const MatArgs& a, int64_t mn0, int64_t kb, int64_t ke, int wave, int lane) {
+  __host__ __device__ __forceinline__ void init(const MatArgs& a, int64_t mn0, int64_t kb, int64_t ke, int wave,
+                                                int lane) {
     ld = a.ld, MN = a.MN, K = a.K, kbeg = kb, kend = ke;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
@@ -170,14 +173,18 @@ struct MatLoader {
 #pragma unroll
     for (int i = 0; i < L; ++i) v[i] = load_chunk<ES>(kb + off[i]);
   }
+  // elements by which chunk i of the last step (from kbeg) is moved back to lie in the operand
+  __host__ __device__ __forceinline__ int64_t last_back(int i) const {
+    const int64_t over = KC ? kbeg + kpos[i] + E - K : (int64_t)(off[i] / ES) - ((K - 1 - kbeg) * ld + MN - E);
+    return over > 0 ? over : 0;
+  }
   // the last step (from kbeg): k past kend is cleared, chunks past the
   // operand's end are fetched from inside it
   __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) {
     f.keep = f.shift = 0;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
-      const int64_t over = KC ? kbeg + kpos[i] + E - K : (int64_t)(off[i] / ES) - ((K - 1 - kbeg) * ld + MN - E);
-      const int64_t d = over > 0 ? over : 0, left = kend - (kbeg + kpos[i]);
+      const int64_t d = last_back(i), left = kend - (kbeg + kpos[i]);
       v[i] = load_chunk<ES>(base + ((int64_t)off[i] - d * ES));
       const int hi = left <= 0 ? 0 : !KC || left > E ? E : (int)left;
       f.keep |= keep_bits(0, hi) << (8 * i);

@@ -36,10 +36,12 @@ void run_layout(mdnn_layout_t layout, const reg::MatArgs& a, const reg::MatArgs&
 }
 
 // one operand: chunks of 16 bytes along its contiguous dimension lie inside
-// it, byte offsets (within the operand, or within one K step) in 32 bits
+// it, byte offsets (within the operand, or within one K step) in 32 bits.  A
+// K step's chunks reach bk elements from a row's start also where K is
+// shorter, and their offsets are formed before they are moved back inside.
 bool operand_ok(int64_t es, bool kc, int64_t MN, int64_t ld, int64_t K) {
   const int64_t e = 16 / es, bk = 128 / es;
-  if (kc) return K >= e && (MN - 1) * ld + K < ((int64_t)1 << 32) / es;
+  if (kc) return K >= e && (MN - 1) * ld + (K > bk ? K : bk) < ((int64_t)1 << 32) / es;
   return MN >= e && bk * ld + MN < ((int64_t)1 << 32) / es;
 }
 
