@@ -14,6 +14,7 @@ namespace mdnn {
 namespace {
 
 using reg::El;
+using reg::end_shift;
 using reg::keep_bits;
 using reg::keep_chunk;
 using reg::load_chunk;
@@ -67,7 +68,7 @@ __global__ void __launch_bounds__(256, 2) conv_gather_kernel(GatherArgs a, Epilo
       const int o = (n * a.rows + row[s]) * a.len + pos[s], from = reg::clampi(o, 0, a.w_total - E);
       const uint32_t keep = row[s] < a.rows ? keep_bits(0, reg::clampi(a.len - pos[s], 0, E)) : 0u;
       uint4 c = load_chunk<ES>((const char*)a.w + (uint32_t)from * (uint32_t)ES);
-      if (__any(o != from)) c = shift_chunk<ES>(c, o - from > -E && o - from < E ? o - from : 0);
+      if (__any(o != from)) c = shift_chunk<ES>(c, end_shift<E>(o, a.w_total));
       wf[s][j] = keep_chunk<ES>(c, keep, 0);
     }
   float bias[NF][4];
@@ -103,10 +104,7 @@ __global__ void __launch_bounds__(256, 2) conv_gather_kernel(GatherArgs a, Epilo
     constexpr bool FULL = decltype(full)::value;
     if (G.shift) {
 #pragma unroll
-      for (int s = 0; s < KS; ++s) {
-        const int o = G.base + rel[s], d = o - reg::clampi(o, 0, a.x_total - E);
-        G.v[s] = shift_chunk<ES>(G.v[s], d > -E && d < E ? d : 0);
-      }
+      for (int s = 0; s < KS; ++s) G.v[s] = shift_chunk<ES>(G.v[s], end_shift<E>(G.base + rel[s], a.x_total));
     }
     float4_t acc[1][1][NF];
 #pragma unroll

@@ -150,8 +150,8 @@ __device__ __forceinline__ int4_t make_rsrc(const void* p, uint32_t bytes) {
 
 // x / d for x * (d - 1) < 2^32, with magic = ceil(2^32 / d) (d >= 2); d == 1
 // is passed as magic 0.
-__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t magic) {
-  return magic ? __umulhi(x, magic) : x;
+__host__ __device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t magic) {
+  return magic ? (uint32_t)(((uint64_t)x * magic) >> 32) : x;
 }
 
 // ---------------------------------------------------------------- loaders

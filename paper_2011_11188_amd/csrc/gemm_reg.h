@@ -82,6 +82,7 @@ constexpr uint32_t keep_all() {
 __device__ __forceinline__ uint32_t keep_bits(int lo, int hi) {
   return lo < hi ? ((1u << hi) - 1u) & ~((1u << lo) - 1u) : 0u;
 }
+// (|d| below the chunk's elements)
 template <int ES>
 __device__ __forceinline__ uint4 shift_chunk(uint4 v, int d) {
   constexpr int B = 8 * ES;
@@ -214,7 +215,16 @@ struct RunArgs {
   int64_t M;               // output pixels (RunRowsLoader), filters (RunFilter)
 };
 
-__device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
+__host__ __device__ __forceinline__ int clampi(int v, int lo, int hi) { return v < lo ? lo : v > hi ? hi : v; }
+
+// How far a chunk wanted at element o of `total` is shifted after it was
+// fetched from inside: 0 where nothing of it is kept (shift_chunk takes less
+// than a chunk).
+template <int E>
+__host__ __device__ __forceinline__ int end_shift(int o, int total) {
+  const int d = o - clampi(o, 0, total - E);
+  return d > -E && d < E ? d : 0;
+}
 
 // elements kept of an image chunk: x position q of its first element in the
 // image row (wsC elements), `left` elements left in the run
@@ -232,10 +242,7 @@ __device__ __forceinline__ void run_load_last(Loader& ld, uint4 (&v)[L], LastFix
   f.keep = g.keep;
   f.shift = 0;
 #pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int d = (int)ld.shift(0, i);
-    f.shift |= pack_shift(d > -Loader::E && d < Loader::E ? d : 0, i);
-  }
+  for (int i = 0; i < L; ++i) f.shift |= pack_shift(ld.shift(0, i), i);
 }
 
 // Rows = output pixels, k = (filter row, run): forward x, and dy of backward
@@ -252,7 +259,7 @@ struct RunRowsLoader {
   uint32_t magic;
   int32_t base[L], iy[L], jc[L], kc[P];
 
-  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
+  __host__ __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
     p = (const char*)a.p, total = a.total, rows = a.rows, len = a.L, lp = a.Lp, hs = a.hs, wsC = a.wsC;
     magic = a.magic_lp, k0 = (int32_t)kb;
     const int32_t hw = a.ho * a.wo;
@@ -273,7 +280,7 @@ struct RunRowsLoader {
       }
     }
   }
-  __device__ __forceinline__ void where(int t, int par, int& r, int& e) {
+  __host__ __device__ __forceinline__ void where(int t, int par, int& r, int& e) {
     const uint32_t k = (uint32_t)(k0 + t * BK + kc[par]);
     r = (int)fast_div(k, magic);
     e = (int)k - r * lp;
@@ -299,11 +306,10 @@ struct RunRowsLoader {
     f.shift = __any(any);
   }
   __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
-  __device__ __forceinline__ int shift(int t, int i) {
+  __host__ __device__ __forceinline__ int shift(int t, int i) {
     int r, e;
     where(t, i % P, r, e);
-    const int o = base[i] + r * wsC + e;
-    return o - clampi(o, 0, total - E);
+    return end_shift<E>(base[i] + r * wsC + e, total);
   }
 };
 
@@ -319,7 +325,7 @@ struct RunFilterLoader {
   uint32_t magic;
   int32_t base[L], kc[P];
 
-  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
+  __host__ __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
     p = (const char*)a.p, total = a.total, rows = a.rows, len = a.L, lp = a.Lp, magic = a.magic_lp, k0 = (int32_t)kb;
 #pragma unroll
     for (int i = 0; i < L; ++i) {
@@ -330,7 +336,7 @@ struct RunFilterLoader {
       base[i] = (int32_t)m * a.rows * a.L;
     }
   }
-  __device__ __forceinline__ void where(int t, int par, int& r, int& e) {
+  __host__ __device__ __forceinline__ void where(int t, int par, int& r, int& e) {
     const uint32_t k = (uint32_t)(k0 + t * BK + kc[par]);
     r = (int)fast_div(k, magic);
     e = (int)k - r * lp;
@@ -357,11 +363,10 @@ struct RunFilterLoader {
     f.shift = __any(any);
   }
   __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
-  __device__ __forceinline__ int shift(int t, int i) {
+  __host__ __device__ __forceinline__ int shift(int t, int i) {
     int r, e;
     where(t, i % P, r, e);
-    const int o = base[i] + r * len + e;
-    return o - clampi(o, 0, total - E);
+    return end_shift<E>(base[i] + r * len + e, total);
   }
 };
 
@@ -378,7 +383,7 @@ struct RunFilterTLoader {
   uint32_t magic, magic_f;
   int32_t col[L], krow[L];
 
-  __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
+  __host__ __device__ __forceinline__ void init(const RunArgs& a, int64_t mn0, int64_t kb, int64_t, int wave, int lane) {
     p = (const char*)a.p, total = a.total, rows = a.rows, len = a.L, lp = a.Lp, nf = a.hs, S = a.wsC, C = a.C;
     magic = a.magic_lp, magic_f = a.magic_a, k0 = (int32_t)kb;
 #pragma unroll
@@ -389,7 +394,7 @@ struct RunFilterTLoader {
       krow[i] = q.r;
     }
   }
-  __device__ __forceinline__ bool where(int t, int i, int& o) {
+  __host__ __device__ __forceinline__ bool where(int t, int i, int& o) {
     const uint32_t k = (uint32_t)(k0 + t * BK + krow[i]);
     const int r = (int)fast_div(k, magic), e = (int)k - r * lp;
     const int s = (int)fast_div((uint32_t)e, magic_f), f = e - s * nf;
@@ -411,10 +416,10 @@ struct RunFilterTLoader {
     f.shift = __any(any);
   }
   __device__ __forceinline__ void load_last(uint4 (&v)[L], LastFix& f) { run_load_last(*this, v, f); }
-  __device__ __forceinline__ int shift(int t, int i) {
+  __host__ __device__ __forceinline__ int shift(int t, int i) {
     int o;
     where(t, i, o);
-    return o - clampi(o, 0, total - E);
+    return end_shift<E>(o, total);
   }
 };
 
@@ -498,8 +503,7 @@ struct RunColsLoader {
     const int32_t px = k0 + t * BK + c.r, q1 = px / wo, n = q1 / ho;
     const int32_t at = (int32_t)(((uint32_t)n * (uint32_t)hs + (uint32_t)(q1 - n * ho + r - padr)) * (uint32_t)wsC +
                                  (uint32_t)((px - q1 * wo - pads) * C + e));
-    const int32_t d = at - clampi(at, 0, total - E);
-    return d > -E && d < E ? d : 0;  // (further off: nothing of the chunk is kept)
+    return end_shift<E>(at, total);
   }
 };
 
@@ -570,7 +574,7 @@ __device__ __forceinline__ void commit(char* dst, int t, const uint4 (&v)[L], co
 #pragma unroll
       for (int i = 0; i < L; ++i) {
         uint4 c = v[i];
-        if (f.shift) c = shift_chunk<ES>(c, (int)ld.shift(t, i));
+        if (f.shift) c = shift_chunk<ES>(c, ld.shift(t, i));
         *(uint4*)(dst + i * 1024) = keep_chunk<ES>(c, f.keep, i);
       }
       return;

@@ -53,3 +53,14 @@ def test_k_contiguous_chunks_stay_inside_the_operand(host, lib, dt, es):
                 if ok(dt, 1, 64, rows, k, k, ld, 1):
                     assert outside(dt, rows, ld, k) == 0, (k, ld, rows, "B")
     assert admitted > 100
+
+
+@pytest.mark.parametrize("dt", [0, 1])
+@pytest.mark.parametrize("shape", [(2, 11, 9, 3, 64, 7, 3), (2, 6, 7, 3, 130, 3, 1), (5, 13, 11, 17, 33, 3, 1),
+                                   (2, 7, 5, 65, 67, 3, 0), (1, 9, 1, 20, 129, 3, 1), (2, 5, 6, 12, 9, 1, 0)])
+def test_run_chunks_are_shifted_by_less_than_a_chunk(host, shape, dt):
+    """Chunks that lie wholly outside an image or filter are not kept, and must
+    not be shifted either: a shift of a whole chunk or more is undefined."""
+    f = host.host_conv_bad_shifts
+    f.restype = C.c_int64
+    assert f(dt, *shape) == 0
