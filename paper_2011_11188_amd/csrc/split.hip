@@ -178,7 +178,8 @@ SplitOp split_op(int64_t rows, int64_t cols, const float* x, int64_t ldx, float 
 mdnn_status_t launch_split(const SplitOp& a, const SplitOp& b, float* ab_scale, hipStream_t st) {
   const int64_t blocks = a.blocks + b.blocks;
   if (blocks == 0) return MDNN_SUCCESS;
-  const unsigned grid = blocks > ((int64_t)1 << 24) ? 1u << 24 : (unsigned)blocks;  // (the kernel loops past it)
+  // a launch holds fewer than 2^32 threads; the kernel loops past the grid
+  const unsigned grid = blocks > ((int64_t)1 << 20) ? 1u << 20 : (unsigned)blocks;
   hipLaunchKernelGGL(split_f16_kernel, dim3(grid), dim3(256), 0, st, a, b, ab_scale);
   return check_launch("split_f16_kernel");
 }

@@ -38,6 +38,20 @@ def test_split_bit_exact(mdnn, rows, cols, scale):
     assert np.array_equal(host64(lo), l)
 
 
+def test_split_tall_matrix(mdnn):
+    """More row pieces than one launch's threads could hold at a block each
+    (2^24 blocks of 256), fixed and automatic scale."""
+    import torch
+    rows = (1 << 24) + 3
+    x = np.resize(_fp32((4099, 1), 23, 1), (rows, 1))
+    h, l = ops.split_f16(x[:4099].astype(np.float64), 1.0)
+    for scale in (1.0, 0.0):
+        hi, lo = mdnn.split_f16(dev(x, "f32"), scale)[:2]
+        if not scale:
+            h, l = ops.split_f16(x[:4099].astype(np.float64), ops.split_scale(x[:4099]))
+        assert np.array_equal(host64(hi), np.resize(h, (rows, 1))) and np.array_equal(host64(lo), np.resize(l, (rows, 1)))
+
+
 def test_split_fp16_inputs_have_zero_second_term(mdnn):
     import torch
     x = W.normal((64, 64), 22, 1, "f16").astype(np.float32)
