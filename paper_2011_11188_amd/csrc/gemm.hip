@@ -470,7 +470,8 @@ static mdnn_status_t colsum_launch(const void* xv, const void* yv, int64_t rows,
   const S* y = (const S*)yv;
   const size_t need = column_sums_ws_bytes(rows, cols);
   const unsigned bx = (unsigned)ceil_div(cols, 64);
-  if (rows <= COLSUM_ONCE_ROWS && rows > 0 && cols >= 8) {
+  // (blocks of 1024 threads: a launch holds fewer than 2^32 threads)
+  if (rows <= COLSUM_ONCE_ROWS && rows > 0 && cols >= 8 && bx < (1u << 22)) {
     hipLaunchKernelGGL((colsum_once_kernel<T, MASK>), dim3(bx), dim3(1024), 0, st, x, y, rows, cols, out);
   } else if (rows <= COLSUM_ROWS) {
     // one chunk: pass 1 alone gives the sums

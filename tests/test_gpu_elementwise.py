@@ -154,6 +154,17 @@ def test_column_sums_short(mdnn, shape, dt):
     assert torch.equal(dbm, dbm2)
 
 
+def test_column_sums_wider_than_one_launch_of_large_blocks(mdnn):
+    """2^28 columns and more: 64 of them per block of 1024 threads would be
+    the 2^32 threads that no launch holds."""
+    import torch
+    cols = (1 << 28) + 70
+    dy = torch.randint(-2048, 2048, (1, cols), dtype=torch.int16, device="cuda").to(torch.float16)
+    db = torch.full((cols,), float("nan"), device="cuda")
+    mdnn.mdnn_bias_act_bwd(1, cols, dy, None, mdnn.ACT_NONE, None, db, DT["f16"])
+    assert bool((db == dy[0]).all())
+
+
 # c = 12: element-wise kernels; c = 16 and 64 (16-bit types): eight channels
 # per thread with 16-byte accesses
 @pytest.mark.parametrize("c", [12, 16, 64])
