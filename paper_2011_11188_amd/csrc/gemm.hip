@@ -261,12 +261,15 @@ colsum_partial_kernel(const typename T::storage* __restrict__ x, const typename 
   }
 }
 
-// Up to COLSUM_ONCE_ROWS rows in one launch: a block of 1024 threads walks
-// all rows of 64 columns (8 column groups x 128 row lanes, eight rows of a
-// thread in flight), then combines the lanes by a fixed tree.  The two-pass
-// form pays a second launch for the same bytes but spreads tall columns over
-// more blocks: at 4096 x 1000 fp32 it takes half the time (1024 x 2048 fp32
-// in one launch 4.5 us, 4097 x 64 in two 5.2 us).
+// More than COLSUM_ROWS and up to COLSUM_ONCE_ROWS rows in one launch: a block
+// of 1024 threads walks all rows of 64 columns (8 column groups x 128 row
+// lanes, eight rows of a thread in flight), then combines the lanes by a fixed
+// tree.  The two-pass form pays a second launch for the same bytes but spreads
+// tall columns over more blocks: at 4096 x 1000 fp32 it takes half the time
+// (1024 x 2048 fp32 in one launch 4.5 us, 4097 x 64 in two 5.2 us).  Up to
+// COLSUM_ROWS rows most of its row lanes have none, and pass 1 on a single
+// chunk is the quicker one at every width (10 to 20000 columns, fp32 and fp16:
+// 2.9-4.6 against 3.1-5.4 us).
 constexpr int64_t COLSUM_ONCE_ROWS = 1024;
 template <class T, bool MASK>
 __global__ void __launch_bounds__(1024)
@@ -462,6 +465,11 @@ size_t column_sums_ws_bytes(int64_t rows, int64_t cols) {
   return (size_t)ceil_div(rows, COLSUM_ROWS) * (size_t)cols * sizeof(float);
 }
 
+// (blocks of 1024 threads: a launch holds fewer than 2^32 threads)
+bool column_sums_once(int64_t rows, int64_t cols) {
+  return rows > COLSUM_ROWS && rows <= COLSUM_ONCE_ROWS && cols >= 8 && ceil_div(cols, 64) < ((int64_t)1 << 22);
+}
+
 template <class T, bool MASK>
 static mdnn_status_t colsum_launch(const void* xv, const void* yv, int64_t rows, int64_t cols, float* out,
                                    void* ws, size_t ws_bytes, hipStream_t st, ReduceBatch* defer) {
@@ -470,8 +478,7 @@ static mdnn_status_t colsum_launch(const void* xv, const void* yv, int64_t rows,
   const S* y = (const S*)yv;
   const size_t need = column_sums_ws_bytes(rows, cols);
   const unsigned bx = (unsigned)ceil_div(cols, 64);
-  // (blocks of 1024 threads: a launch holds fewer than 2^32 threads)
-  if (rows <= COLSUM_ONCE_ROWS && rows > 0 && cols >= 8 && bx < (1u << 22)) {
+  if (column_sums_once(rows, cols)) {
     hipLaunchKernelGGL((colsum_once_kernel<T, MASK>), dim3(bx), dim3(1024), 0, st, x, y, rows, cols, out);
   } else if (rows <= COLSUM_ROWS) {
     // one chunk: pass 1 alone gives the sums

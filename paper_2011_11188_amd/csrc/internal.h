@@ -79,6 +79,8 @@ mdnn_status_t cast_f32_checked(int64_t n, const float* src, void* dst, mdnn_dtyp
 // reduction when a workspace of column_sums_ws_bytes(rows, cols) bytes is
 // given, a single (slower) pass otherwise.
 size_t column_sums_ws_bytes(int64_t rows, int64_t cols);
+// Whether one launch of large blocks takes these column sums (no workspace used).
+bool column_sums_once(int64_t rows, int64_t cols);
 mdnn_status_t column_sums(const void* x, const void* y, mdnn_dtype_t t, int64_t rows, int64_t cols,
                           float* out, void* ws, size_t ws_bytes, hipStream_t stream,
                           ReduceBatch* defer = nullptr);
