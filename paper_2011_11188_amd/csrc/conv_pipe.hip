@@ -183,6 +183,9 @@ SplitPlan conv_pipe_filter_plan(const ConvGeom& g) {
   if (x_bytes > BUF_MAX || K * g.k * 2 > BUF_MAX || Kp * (g.wo - 1) >= ((int64_t)1 << 32) ||
       (Kp / g.wo + 1) * (g.ho - 1) >= ((int64_t)1 << 32))
     return p;
+  // dy's offsets run to the end of the last, possibly ragged, K step: past 32
+  // bits they would come back to dy's first rows in place of zeros
+  if (Kp * g.k * 2 > ((int64_t)1 << 32)) return p;
   if (N > BUF_MAX / 4 || M * N > BUF_MAX / 4) return p;
   // aim at about 256 (64 x 128 tiles, 8 waves) or 512 (64 x 64 tiles, 4
   // waves) workgroups; each split keeps at least 4 K steps and the partials

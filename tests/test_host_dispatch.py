@@ -22,3 +22,31 @@ def test_column_sums_one_launch_rule(lib):
     assert not f(1024, 7)
     for cols in ((1 << 28) - 64, (1 << 28) - 63, 1 << 28, (1 << 28) + 70, 1 << 40):
         assert not f(300, cols) or -(-cols // 64) * 1024 < 2 ** 32
+
+
+class _Geom(C.Structure):
+    _fields_ = [(n, C.c_int32) for n in ("n", "h", "w", "c", "k", "r", "s", "pad", "ho", "wo")]
+
+
+class _Plan(C.Structure):
+    _fields_ = [("splits", C.c_int), ("k_per_split", C.c_int64)]
+
+
+def _geom(n, h, w, c, k, r, pad):
+    return _Geom(n, h, w, c, k, r, r, pad, h + 2 * pad - r + 1, w + 2 * pad - r + 1)
+
+
+def test_direct_to_lds_filter_gradient_offsets_fit_32_bits(lib):
+    """Few pixels and very many output channels: dy's byte offsets up to the end
+    of the padded last K step (64 pixels) stay below 2^32, where the range check
+    turns them into zeros (past it they would wrap to valid rows, and an Inf
+    there would reach the sums as 0 * Inf)."""
+    f = lib["_ZN4mdnn21conv_pipe_filter_planERKNS_8ConvGeomE"]
+    f.argtypes, f.restype = [C.POINTER(_Geom)], _Plan
+    taken = 0
+    for n in (1, 2, 3, 15, 16, 31, 32, 33, 63, 64, 65, 129):
+        for k in [8, 64, 1 << 20] + [(1 << p) + d for p in (24, 25, 26) for d in (-8, 0, 8)]:
+            if f(C.byref(_geom(n, 1, 1, 8, k, 1, 0))).splits:
+                taken += 1
+                assert -(-n // 64) * 64 * k * 2 <= 2 ** 32, (n, k)
+    assert taken > 40
