@@ -22,6 +22,10 @@ mdnn_status_t conv_pipe_fwd(const ConvGeom& g, const void* x, const void* w, con
 mdnn_status_t conv_pipe_bwd_data(const ConvGeom& g, const void* dy, const void* w, const Epilogue& ep,
                                  mdnn_dtype_t io, mdnn_dtype_t out, hipStream_t st, bool* done);
 
+// Whether one launch holds an M x N output of the loaders for channel counts
+// that are a multiple of 8 but not of 64.
+bool conv_pipe_runs_fit(int64_t M, int64_t N);
+
 // Split plan of the pipelined backward-filter GEMM (M = c_out,
 // N = r*s*c_in, K = n*ho*wo), or splits == 0 when the shape is not eligible:
 // c_in, c_out multiples of 8, x and dy below 2^31 bytes.  A function of the shape only.

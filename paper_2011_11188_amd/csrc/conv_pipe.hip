@@ -118,6 +118,14 @@ mdnn_status_t runs8_dispatch(const lds::ConvRunsArgs& a, const ConvGeom& g, cons
   return run_runs8<T, OutT, TileSquare, BWD>(a, g, w, M, N, K, ep, st);
 }
 
+}  // namespace
+
+// A launch holds fewer than 2^32 threads: the runs loaders' widest tiles take
+// 512 per 128 x 128 or 256 x 64 outputs.
+bool conv_pipe_runs_fit(int64_t M, int64_t N) { return (M + 256) * ceil_div(N, 128) < ((int64_t)1 << 30); }
+
+namespace {
+
 // rows over an ho x wo grid gathered from src [n][hs][ws][c]
 template <bool BWD>
 mdnn_status_t conv_pipe_runs8(const ConvGeom& g, const void* src, int32_t hs, int32_t ws, int32_t c, int32_t ho,
@@ -125,7 +133,7 @@ mdnn_status_t conv_pipe_runs8(const ConvGeom& g, const void* src, int32_t hs, in
                               mdnn_dtype_t io, mdnn_dtype_t out, hipStream_t st, bool* done) {
   const int64_t M = (int64_t)g.n * ho * wo, len = (int64_t)g.s * c, K = g.r * len;
   const int64_t bytes = (int64_t)g.n * hs * ws * c * 2, w_bytes = (int64_t)g.k * g.r * g.s * g.c * 2;
-  if (bytes > BUF_MAX || w_bytes > BUF_MAX || M > BUF_MAX || (K + 64) * (len > g.k ? len : g.k) >= ((int64_t)1 << 32))
+  if (bytes > BUF_MAX || w_bytes > BUF_MAX || !conv_pipe_runs_fit(M, N) || (K + 64) * (len > g.k ? len : g.k) >= ((int64_t)1 << 32))
     return MDNN_SUCCESS;
   const lds::ConvRunsArgs a{src, (uint32_t)bytes, hs,           ws * c, c,    ho, wo, g.r, (int32_t)len, magic_of((uint32_t)len),
                             padr, pads,           M};

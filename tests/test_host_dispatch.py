@@ -50,3 +50,17 @@ def test_direct_to_lds_filter_gradient_offsets_fit_32_bits(lib):
                 taken += 1
                 assert -(-n // 64) * 64 * k * 2 <= 2 ** 32, (n, k)
     assert taken > 40
+
+
+def test_direct_to_lds_convolution_launches_stay_below_2_32_threads(lib):
+    """More output pixels than 512 threads per 128 x 128 or 256 x 64 tile leave
+    room for go to the general kernel, whose launch still holds them."""
+    fit = lib["_ZN4mdnn18conv_pipe_runs_fitEll"]
+    fit.argtypes, fit.restype = [C.c_int64, C.c_int64], C.c_bool
+    taken = 0
+    for n in (1, 64, 65, 72, 128, 129, 1000):
+        for m in [64, 1 << 20] + [(1 << p) + d for p in (27, 28, 29, 30, 31) for d in (-300, -1, 0)]:
+            if fit(m, n):
+                taken += 1
+                assert 512 * max(-(-m // 128) * -(-n // 128), -(-m // 256) * -(-n // 64)) < 2 ** 32, (m, n)
+    assert taken > 30 and all(fit(1 << 20, n) for n in (1, 64, 200, 1000))
