@@ -97,15 +97,19 @@ struct SplitOp {
   float inv_scale;
   const float* scale_dev;
   const uint32_t* bits;
-  int64_t chunks;  // blocks per row
-  int64_t blocks;  // blocks of this operand
+  int32_t lanes_log2;  // threads per row piece, four columns each
+  int64_t chunks;      // pieces per row
+  int64_t blocks;      // blocks of this operand
 };
-constexpr int SPLIT_COLS = 1024;  // columns per block, four per thread
+constexpr int SPLIT_LANES_LOG2 = 8;  // a piece has at most a block's 256 threads
 
 // Blocks of both operands of a product in one launch (op b may be empty).
 // HBM-bound (4 B read, 4 B written per element): four elements per thread by
 // unaligned 16- and 8-byte accesses; element by element, one launch per
-// operand, two 2048 x 2048 operands took 21 us.  ab_scale (nullable) receives
+// operand, two 2048 x 2048 operands took 21 us.  A block holds as many rows as
+// their pieces leave room for: with one row per block tall narrow matrices are
+// bound by block launches (56512 x 114 38.5 -> 11.4 us, 184512 x 31 119 -> 13).
+// ab_scale (nullable) receives
 // the product of the two automatic or fixed scales.
 __global__ void __launch_bounds__(256) split_f16_kernel(SplitOp a, SplitOp b, float* ab_scale) {
   for (int64_t g = blockIdx.x; g < a.blocks + b.blocks; g += gridDim.x) {
@@ -117,8 +121,10 @@ __global__ void __launch_bounds__(256) split_f16_kernel(SplitOp a, SplitOp b, fl
     if (o.bits) inv = 1.0f / auto_scale(*o.bits);
     if (ab_scale && g == 0 && threadIdx.x == 0)
       *ab_scale = (a.bits ? auto_scale(*a.bits) : 1.0f / a.inv_scale) * (b.bits ? auto_scale(*b.bits) : 1.0f / b.inv_scale);
-    const int64_t row = blk / o.chunks, c = (blk - row * o.chunks) * SPLIT_COLS + threadIdx.x * 4;
-    if (c >= o.cols) continue;
+    const int64_t grp = blk / o.chunks, piece = blk - grp * o.chunks;
+    const int lane = threadIdx.x & ((1 << o.lanes_log2) - 1), sub = threadIdx.x >> o.lanes_log2;
+    const int64_t row = (grp << (SPLIT_LANES_LOG2 - o.lanes_log2)) + sub, c = ((piece << o.lanes_log2) + lane) * 4;
+    if (row >= o.rows || c >= o.cols) continue;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     const float* p = o.x + row * o.ldx + c;
     if (c + 4 <= o.cols) {
@@ -171,8 +177,14 @@ size_t seg(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
 SplitOp split_op(int64_t rows, int64_t cols, const float* x, int64_t ldx, float scale, const float* scale_dev,
                  const uint32_t* bits, uint16_t* hi, int64_t ldh, uint16_t* lo, int64_t ldl) {
   SplitOp o{x, rows, cols, ldx, hi, lo, ldh, ldl, scale_dev || bits ? 1.0f : 1.0f / scale, scale_dev,
-            bits, ceil_div(cols, (int64_t)SPLIT_COLS), 0};
-  o.blocks = rows * o.chunks;
+            bits, 0, 0, 0};
+  while (o.lanes_log2 < SPLIT_LANES_LOG2 && ((int64_t)4 << o.lanes_log2) < cols) ++o.lanes_log2;
+  // shorter pieces (whole half-waves) where they leave a fifth fewer threads idle
+  const auto threads = [&](int l) { return ceil_div(cols, (int64_t)4 << l) << l; };
+  for (int l = o.lanes_log2; l >= 5; --l)
+    if (threads(l) * 10 <= threads(o.lanes_log2) * 8) o.lanes_log2 = l;
+  o.chunks = ceil_div(cols, (int64_t)4 << o.lanes_log2);
+  o.blocks = ceil_div(rows, (int64_t)1 << (SPLIT_LANES_LOG2 - o.lanes_log2)) * o.chunks;
   return o;
 }
 mdnn_status_t launch_split(const SplitOp& a, const SplitOp& b, float* ab_scale, hipStream_t st) {

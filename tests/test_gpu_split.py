@@ -167,10 +167,11 @@ def test_gemm_split3_full_size_sampled(mdnn):
     assert norm_max_err(sel, exact) < 1e-6
 
 
-# Split and automatic scale at the edges of their 1024-column pieces and
-# 4-column quads, odd leading dimensions and bases; the largest magnitude in
+# Split and automatic scale at the edges of their pieces (of 4 to 1024 columns,
+# 256 to 1 rows of them per block) and 4-column quads, odd leading dimensions and bases; the largest magnitude in
 # the last element, and only in the other operand's range of the product.
-@pytest.mark.parametrize("shape", [(1, 1), (3, 5), (300, 1023), (7, 1025), (2, 4099), (1500, 3)])
+@pytest.mark.parametrize("shape", [(1, 1), (3, 5), (300, 1023), (7, 1025), (2, 4099), (1500, 3), (31, 27), (130, 129),
+                                   (67, 513), (9, 2060), (1025, 1)])
 def test_split_and_scale_edges(mdnn, shape):
     import torch
     rows, cols = shape
