@@ -199,9 +199,11 @@ static size_t filter_ws_split_bytes(const ConvGeom& g, mdnn_dtype_t io) {
   if (q.splits > 1 && (size_t)q.splits > splits) splits = (size_t)q.splits;
   const SplitPlan u = conv_reg_filter_plan(g, io);
   if (u.splits > 1 && (size_t)u.splits > splits) splits = (size_t)u.splits;
-  // the vector-ALU kernels' block count (at least the matrix-core kernel's)
-  const int64_t sb = conv_small_filter_blocks(g, MDNN_F32);
+  // the vector-ALU kernels' block count (at least the matrix-core kernel's
+  // where they take both types' layers)
+  const int64_t sb = conv_small_filter_blocks(g, MDNN_F32), st = conv_small_filter_blocks(g, io);
   if (sb > 0 && (size_t)sb > splits) splits = (size_t)sb;
+  if (st > 0 && (size_t)st > splits) splits = (size_t)st;
   return (splits * mn + 255) & ~(size_t)255;
 }
 
