@@ -57,6 +57,19 @@ def test_conv_multiples_of_8_channels(mdnn, shape, dt):
     _check(mdnn, shape, dt, 8)
 
 
+# Images or filters of less than one 16-byte chunk: read by elements, steps of
+# several filter rows, output channels past 16 and past the filter's chunk.
+TINY = [(1, 1, 1, 1, 1, 1, 1, 0), (7, 1, 1, 1, 2, 3, 3, 1), (3, 1, 1, 2, 9, 3, 3, 1), (1, 2, 2, 1, 40, 2, 2, 1),
+        (9, 5, 7, 3, 2, 1, 1, 0), (300, 4, 3, 7, 1, 1, 1, 0), (2, 1, 1, 3, 33, 5, 5, 4), (4, 9, 1, 1, 1, 7, 1, 0),
+        (1, 1, 1, 3, 300, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("shape", TINY)
+def test_conv_below_a_chunk(mdnn, shape, dt):
+    _check(mdnn, shape, dt, 1)
+
+
 def _check(mdnn, shape, dt, gap):
     """All three passes, each operand `gap` elements into a buffer of NaN."""
     import torch
