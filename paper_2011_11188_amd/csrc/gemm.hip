@@ -842,7 +842,14 @@ static mdnn_status_t gemm_dispatch32(mdnn_layout_t layout, int64_t M, int64_t N,
   // fp32 on the matrix cores (157 TFLOP/s; the vector-ALU kernel below stays
   // under 79): NN 1024 x 2048 x 2048 198 -> 87 us, 4096^3 2045 -> 1008 us,
   // 1000^3 89 -> 29 us.  Contiguous extents below 4 keep the kernel below.
-  if (gemm_reg_ok(MDNN_F32, layout, M, N, K, lda, ldb, splits)) {
+  // Nor products of few K steps and many outputs in 16-byte rows: those are
+  // stores, and a K step below that is half as long and six workgroups of which
+  // fit a CU wastes less before them (TN 7718 x 6080 x 8: 42 us, 60 on the
+  // matrix cores, 1600 x 6016 x 16 13.1 and 19.5, NT 3115 x 1472 x 45 14.4 and
+  // 19.0; K of 64 level at 2^21 outputs; unaligned rows are quicker above).
+  const int64_t few_outputs = layout == MDNN_TN ? 1 << 20 : 1 << 17;
+  const bool shallow = splits == 1 && ep.vec4 && ((K <= 16 && M * N >= few_outputs) || (K <= 48 && M * N >= 1 << 21));
+  if (!shallow && gemm_reg_ok(MDNN_F32, layout, M, N, K, lda, ldb, splits)) {
     MDNN_TRY(gemm_reg(MDNN_F32, MDNN_F32, layout, M, N, K, A, lda, B, ldb, ep, splits, st));
     return split ? reduce_epilogue<F32, F32>(ws, splits, M, N, ep_in, st) : MDNN_SUCCESS;
   }

@@ -786,10 +786,12 @@ gemm_reg_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
 }
 
 // 128 x 128 with waves of 64 x 64; 128 x 64 and 64 x 64 for narrow products
-// and small grids
+// and small grids; 64 x 64 in at most 128 registers for 16-bit products of one
+// or two K steps
 typedef lds::Tile<128, 128, 2, 2, 2> TileR128;
 typedef lds::Tile<128, 64, 2, 2, 2> TileR128x64;
 typedef lds::Tile<64, 64, 2, 2, 2> TileR64;
+typedef lds::Tile<64, 64, 2, 2, 4> TileR64Shallow;
 
 }  // namespace reg
 }  // namespace mdnn

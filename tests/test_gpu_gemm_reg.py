@@ -29,12 +29,28 @@ def mdnn():
 SHAPES = [(9, 8, 9), (65, 63, 64), (64, 64, 65), (127, 129, 31), (130, 66, 33), (33, 257, 321), (200, 72, 129),
           (2050, 2049, 70)]
 
+# Few K steps and many outputs, either side of the rules that pick a kernel or
+# tile for them: 2^17, 2^18, 2^20 and 2^21 outputs, K of 16, 48 and 128, 384 tiles
+# of 128 x 128.
+SHALLOW = [(361, 364, 16), (513, 516, 5), (510, 513, 9), (700, 375, 128), (701, 375, 129), (1023, 1028, 16),
+           (1023, 1028, 17), (1449, 1452, 48), (1449, 1452, 49), (2433, 2561, 65), (2432, 2560, 128)]
+
 
 @pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
 @pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
 def test_register_staged_any_alignment(mdnn, layout, dt):
+    _check(mdnn, layout, dt, SHAPES)
+
+
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("layout", ["NN", "NT", "TN"])
+def test_register_staged_few_steps(mdnn, layout, dt):
+    _check(mdnn, layout, dt, SHALLOW)
+
+
+def _check(mdnn, layout, dt, shapes):
     import torch
-    for i, (m, n, k) in enumerate(SHAPES):
+    for i, (m, n, k) in enumerate(shapes):
         sa = (k, m) if layout == "TN" else (m, k)
         sb = (n, k) if layout == "NT" else (k, n)
         a = W.normal(sa, 51, 10 * i + 1, dt)
