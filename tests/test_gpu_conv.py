@@ -122,7 +122,7 @@ PIPE = [  # n, h, w, c_in, c_out, r, s, pad
     (3, 5, 6, 128, 64, 3, 3, 0),     # fwd + bwd_data with ho != h (valid conv)
     (2, 8, 8, 64, 128, 5, 5, 2),     # all three; filter single split
     (4, 16, 16, 64, 64, 1, 1, 0),    # 1x1; filter split-K on the 64-row tile
-    (2, 12, 10, 192, 40, 3, 3, 1),   # fwd, N = 40 (256 x 64 tile)
+    (2, 12, 10, 192, 40, 3, 3, 1),   # fwd, N = 40 (128 x 64 tile)
     (5, 11, 13, 64, 64, 3, 3, 1),    # ragged M = 715
     (8, 16, 16, 64, 256, 3, 3, 1),   # filter split-K on the 128 x 128 tile
     (2, 8, 8, 16, 8, 3, 3, 1),       # filter with c_out = 8
@@ -140,17 +140,16 @@ def test_conv_pipelined_against_oracle(mdnn, shape, dt):
     assert norm_max_err(db, dy.sum(axis=(0, 1, 2))) <= TOL
 
 
-# Forward on the pipelined kernel with c_in a multiple of 32 but not of 64:
-# two 32-channel half blocks per K step, the K range padded to whole steps
-# (odd half-block counts: 3x3, 1x1, 5x3 taps at c_in = 32), several half
-# blocks per tap (c_in = 96, 160), both tile shapes, ragged M, valid and
-# wider padding.
+# Forward with c_in a multiple of 32 but not of 64: runs of a filter row's
+# elements, the K range padded to whole steps (3x3, 5x3 taps at c_in = 32; 1x1
+# is gathered), several steps per tap (c_in = 96, 160), both tile
+# shapes, ragged M, valid and wider padding.
 PIPE32 = [  # n, h, w, c_in, c_out, r, s, pad
-    (2, 14, 14, 32, 64, 5, 5, 2),    # LeNet conv2 shape at batch 2 (25 taps: a padded half block)
-    (3, 7, 9, 32, 40, 3, 3, 1),      # 9 taps, 256 x 64 tile, ragged M = 189
-    (2, 6, 5, 32, 72, 1, 1, 0),      # 1x1: one real half block per step, 128 x 128 tile
-    (2, 9, 7, 96, 24, 3, 3, 0),      # three half blocks per tap, valid padding
-    (1, 8, 11, 160, 136, 5, 3, 2),   # five half blocks per tap, 5x3 taps, N = 136
+    (2, 14, 14, 32, 64, 5, 5, 2),    # LeNet conv2 shape at batch 2 (25 taps: half a step of padding)
+    (3, 7, 9, 32, 40, 3, 3, 1),      # 9 taps, 128 x 64 tile, ragged M = 189
+    (2, 6, 5, 32, 72, 1, 1, 0),      # 1x1: gathered
+    (2, 9, 7, 96, 24, 3, 3, 0),      # one and a half steps per tap, valid padding
+    (1, 8, 11, 160, 136, 5, 3, 2),   # two and a half steps per tap, 5x3 taps, N = 136
 ]
 
 
@@ -166,8 +165,8 @@ def test_conv_fwd_32_channel_blocks_against_oracle(mdnn, shape, dt):
 
 def test_conv_fwd_32_channel_blocks_epilogue_and_integers(mdnn):
     """The same path with bias + ReLU into bf16 (bound as for the other
-    pipelined forward), and bit-exact on small integers (the padded half
-    block contributes exact zeros)."""
+    pipelined forward), and bit-exact on small integers (the padding of the
+    last step contributes exact zeros)."""
     import torch
     n, h, w, ci, co, r, s, pad = 3, 9, 7, 32, 48, 3, 3, 1
     x = W.normal((n, h, w, ci), 24, 1, "bf16", 0.3)

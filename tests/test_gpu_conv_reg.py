@@ -25,11 +25,14 @@ def mdnn():
 # (n, h, w, c_in, c_out, r, s, pad): three channels with wide filters (runs of
 # 21, 15, 9), a run one over and one under a chunk, channels either side of 64
 # and 128, one-pixel-wide images, valid and over-wide padding, r != s, a
-# tall output (128 x 64 tiles), split filter gradients with a ragged last step.
+# tall output (128 x 64 tiles backward, gathered forward), split filter gradients with a ragged last step.
 SHAPES = [
     (2, 11, 9, 3, 64, 7, 7, 3), (3, 8, 8, 3, 70, 5, 5, 2), (2, 6, 7, 3, 130, 3, 3, 1), (5, 13, 11, 17, 33, 3, 3, 1),
     (2, 7, 5, 65, 67, 3, 3, 0), (1, 9, 1, 20, 129, 3, 3, 1), (2, 5, 6, 12, 9, 1, 1, 0), (2, 4, 5, 100, 12, 1, 5, 2),
     (3, 6, 6, 10, 11, 2, 4, 3), (2, 180, 190, 7, 60, 3, 3, 1), (4, 30, 31, 5, 13, 3, 3, 1),
+    # 128 x 128 tiles in both directions (518 of them forward, also enough for
+    # fp32); 128 x 64 forward with a reduction too long to be gathered
+    (2, 182, 184, 70, 70, 1, 3, 0), (2, 182, 184, 70, 60, 1, 3, 0),
 ]
 
 
@@ -43,11 +46,14 @@ def test_conv_any_channels(mdnn, shape, dt):
 # kernel: one chunk per tap, a K step over several taps and filter rows, K and
 # pixel counts that end inside a step, valid and over-wide padding (filter
 # gradients whose output grid is not the input's), outputs that take the 256 x
-# 64 tile past 128 columns (200) and the 64 x 128 one, one-pixel-wide images.
+# 64 tile past 128 columns (200), the 128 x 64 and the 64 x 128 one, one-pixel-wide images.
 SHAPES8 = [
     (2, 9, 7, 8, 16, 3, 3, 1), (3, 8, 8, 24, 40, 5, 5, 2), (2, 7, 9, 72, 88, 3, 3, 0), (1, 6, 5, 16, 8, 3, 3, 2),
     (4, 13, 1, 40, 136, 3, 3, 1), (2, 10, 11, 48, 200, 1, 1, 0), (9, 11, 13, 96, 80, 5, 5, 2), (2, 5, 6, 104, 72, 2, 4, 3),
     (3, 90, 91, 8, 200, 3, 3, 1), (5, 12, 13, 64, 64, 3, 3, 0), (2, 6, 6, 8, 8, 7, 7, 3),
+    # narrow outputs of 66248 and 66976 pixels: 256 x 64 tiles, not 128 x 64, by
+    # the 64-channel loaders one way and the runs of 40 channels the other
+    (2, 182, 184, 64, 40, 1, 3, 0), (2, 182, 184, 40, 64, 1, 3, 0),
 ]
 
 
