@@ -179,10 +179,6 @@ SplitOp split_op(int64_t rows, int64_t cols, const float* x, int64_t ldx, float 
   SplitOp o{x, rows, cols, ldx, hi, lo, ldh, ldl, scale_dev || bits ? 1.0f : 1.0f / scale, scale_dev,
             bits, 0, 0, 0};
   while (o.lanes_log2 < SPLIT_LANES_LOG2 && ((int64_t)4 << o.lanes_log2) < cols) ++o.lanes_log2;
-  // shorter pieces (whole half-waves) where they leave a fifth fewer threads idle
-  const auto threads = [&](int l) { return ceil_div(cols, (int64_t)4 << l) << l; };
-  for (int l = o.lanes_log2; l >= 5; --l)
-    if (threads(l) * 10 <= threads(o.lanes_log2) * 8) o.lanes_log2 = l;
   o.chunks = ceil_div(cols, (int64_t)4 << o.lanes_log2);
   o.blocks = ceil_div(rows, (int64_t)1 << (SPLIT_LANES_LOG2 - o.lanes_log2)) * o.chunks;
   return o;
