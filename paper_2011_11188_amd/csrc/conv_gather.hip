@@ -55,10 +55,10 @@ __device__ __forceinline__ uint4 tiny_chunk(const void* p, int o, int total) {
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// TINY_X: an image tensor of less than one chunk, read by elements; a filter of
-// less than one is loaded so in any case, once per wave (6 -> 1 channels, 1x1,
-// 222 x 31 x 31: 5 us, 91 in the general kernel, which would be left).
-template <class T, class OutT, int KS, int NF, bool TINY_X = false>
+// TINY: the filter (1) or filter and image (2) are read by elements, for tensors
+// of less than one chunk (6 -> 1 channels, 1x1, 222 x 31 x 31: 5 us, 91 in the
+// general kernel, which would be left).
+template <class T, class OutT, int KS, int NF, int TINY = 0>
 __global__ void __launch_bounds__(256, 2) conv_gather_kernel(GatherArgs a, Epilogue ep) {
   typedef typename OutT::storage DS;
   constexpr int ES = El<T>::ES, E = El<T>::E;
@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(256, 2) conv_gather_kernel(GatherArgs a, Epilo
       const int o = (n * a.rows + row[s]) * a.len + pos[s], from = reg::clampi(o, 0, a.w_total - E);
       const uint32_t keep = row[s] < a.rows ? keep_bits(0, reg::clampi(a.len - pos[s], 0, E)) : 0u;
       uint4 c;
-      if (NF == 1 && a.w_total < E) {
+      if (TINY == 1 || (TINY == 2 && a.w_total < E)) {
         c = tiny_chunk<T>(a.w, o, a.w_total);
       } else {
         c = load_chunk<ES>((const char*)a.w + (uint32_t)from * (uint32_t)ES);
@@ -118,12 +118,12 @@ __global__ void __launch_bounds__(256, 2) conv_gather_kernel(GatherArgs a, Epilo
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int o = G.base + rel[s], from = reg::clampi(o, 0, a.x_total - E);
-      if constexpr (TINY_X)
+      if constexpr (TINY == 2)
         G.v[s] = tiny_chunk<T>(a.x, o, a.x_total);
       else
         G.v[s] = load_chunk<ES>(x + (uint32_t)from * (uint32_t)ES);
       G.keep[s] = run_keep<E>((uint32_t)(y0 + row[s]) < (uint32_t)a.hs, x0 + pos[s], a.wsC, a.len - pos[s]);
-      any |= !TINY_X && o != from && G.keep[s] != 0;
+      any |= TINY < 2 && o != from && G.keep[s] != 0;
     }
     G.shift = __any(any);
   };
@@ -213,10 +213,16 @@ void launch_nf(const GatherArgs& a, const Epilogue& ep, hipStream_t st) {
 
 template <class T, class OutT>
 void launch(const GatherArgs& a, int ks, const Epilogue& ep, hipStream_t st) {
-  if (a.x_total < El<T>::E) {  // (steps past the filter are cleared)
-    const dim3 grid((unsigned)ceil_div((int64_t)a.M, 64), (unsigned)ceil_div((int64_t)a.N, 16));
-    if (ks <= 1) hipLaunchKernelGGL((conv_gather_kernel<T, OutT, 1, 1, true>), grid, dim3(256), 0, st, a, ep);
-    else hipLaunchKernelGGL((conv_gather_kernel<T, OutT, 6, 1, true>), grid, dim3(256), 0, st, a, ep);
+  // (a filter below a chunk has at most 7 rows and 56 padded elements)
+  if (a.x_total < El<T>::E || a.w_total < El<T>::E) {
+    const int64_t by = ceil_div((int64_t)a.N, 16), most = ceil_div((int64_t)1024, by), all = ceil_div((int64_t)a.M, 64);
+    const dim3 grid((unsigned)(all < most ? all : most), (unsigned)by);
+    if (a.x_total >= El<T>::E && ks <= 1)
+      hipLaunchKernelGGL((conv_gather_kernel<T, OutT, 1, 1, 1>), grid, dim3(256), 0, st, a, ep);
+    else if (a.x_total >= El<T>::E)
+      hipLaunchKernelGGL((conv_gather_kernel<T, OutT, 2, 1, 1>), grid, dim3(256), 0, st, a, ep);
+    else if (ks <= 1) hipLaunchKernelGGL((conv_gather_kernel<T, OutT, 1, 1, 2>), grid, dim3(256), 0, st, a, ep);
+    else hipLaunchKernelGGL((conv_gather_kernel<T, OutT, 6, 1, 2>), grid, dim3(256), 0, st, a, ep);
   } else if (ks <= 1) launch_nf<T, OutT, 1>(a, ep, st);
   else if (ks == 2) launch_nf<T, OutT, 2>(a, ep, st);
   else if (ks == 3) launch_nf<T, OutT, 3>(a, ep, st);
@@ -234,6 +240,14 @@ mdnn_status_t conv_gather_fwd(const ConvGeom& g, const void* x, const void* w, c
   const int64_t E = 16 / (int64_t)dtype_size(io), len = (int64_t)g.s * g.c, lp = ceil_div(len, E) * E, K = g.r * lp;
   const int64_t M = (int64_t)g.n * g.ho * g.wo, xt = (int64_t)g.n * g.h * g.w * g.c, wt = (int64_t)g.k * g.r * len;
   const int64_t LIM = (int64_t)1 << 30;
+  // Against the kernels behind this one (register-staged, direct-to-LDS), 4 to
+  // 1024 output channels, 6 to 200 thousand pixels: 0.3-1.0 of their time up to
+  // 64 output channels and for channel counts that are multiples of 4 (3 -> 64,
+  // 3x3, 64 x 56 x 56 fp16 10 against 16 us); up to 1.2 for 64 channels, 1x1, on 128
+  // to 512 (32 x 28 x 28 fp16 -> 256: 11.5 and 9.7) and up to 1.5 for 16-bit rows
+  // on odd elements with a reduction above 128 (3 -> 64, 7x7, 16 x 64 x 64: 20 and
+  // 13.5, but 64 x 64 x 64 34 and 48): a wave's filter loads wait for each other,
+  // which few pixel groups per wave do not make up for.
   if (K > 24 * E || (K > 64 && E == 8 && g.c % 8 == 0)) return MDNN_SUCCESS;
   if (xt >= LIM || wt >= LIM || M + 32 >= LIM || ceil_div(g.k, 16) > 65535 ||
       (M + 32) * (g.wo - 1) >= ((int64_t)1 << 32) || ((M + 32) / g.wo + 1) * (g.ho - 1) >= ((int64_t)1 << 32))

@@ -360,9 +360,11 @@ int64_t conv_small_filter_blocks(const ConvGeom& g, mdnn_dtype_t io) {
   // from 8 output channels on the register-staged kernel takes these layers
   // (1 -> 32 channels, 5x5, 256 x 28 x 28: bf16 26.2 -> 16.8 us, fp32 51.7 ->
   // 31.9 us; 3 -> 16, 3x3, 32 x 32 x 32 fp16 17.8 -> 12.0 us), if it can: its
-  // 16-byte chunks need as many elements of x (2 -> 9 channels, 3x3, three
-  // fp16 pixels: 9.5 us here, 19.7 in the general kernel)
-  if (g.k >= 8 && conv_reg_filter_plan(g, io).splits > 0) return 0;
+  // 16-byte chunks need as many elements of x.  Of the rest 16-bit layers stay
+  // here (2 -> 9 channels, 3x3, three fp16 pixels 9.5 us, 19.7 in the general
+  // kernel; 1 -> 100, 3x3, six 13 and 25), fp32 ones go to the general kernel
+  // (3 -> 11, 3x3, one pixel 7.2, 19.6 here).
+  if (g.k >= 8 && (io == MDNN_F32 || conv_reg_filter_plan(g, io).splits > 0)) return 0;
   if (K > 64 || g.k > 256 || (int64_t)g.k * K > 1024 || filter_lds(g) > LDS_LIMIT || !pixels_fit(g)) return 0;
   const int64_t P = (int64_t)g.n * g.ho * g.wo;
   if (filter_mfma_ok(g, io)) return ceil_div(P, MF_FILTER_PIXELS);
