@@ -801,8 +801,8 @@ static mdnn_status_t gemm_dispatch16(mdnn_layout_t layout, int64_t M, int64_t N,
              gemm_reg_ok(T::id, layout, M, N, K, lda, ldb, splits)) {
     // What the pipelined kernel refuses (odd leading dimensions, K or extents,
     // few tiles).  Against the general kernel below: bf16 NN 1000 x 777 x 1531
-    // 117 -> 17 us, TN 4001 x 3999 x 4003 732 -> 196 us, NN 1000^3 22 -> 12 us,
-    // NN 64 x 64 x 4096 69 -> 21 us.  Where rows are 16-byte aligned and there
+    // 117 -> 14.3 us, TN 4001 x 3999 x 4003 732 -> 190 us, NN 1000^3 22 -> 10 us,
+    // NN 64 x 64 x 4096 69 -> 19 us.  Where rows are 16-byte aligned and there
     // is a 256 x 256 tile per CU the general kernel's larger tile is still
     // better (fp16 NT 7488 x 4032 x 104: 36.6 against 39.0 us).
     MDNN_TRY(gemm_reg(T::id, OutT::id, layout, M, N, K, A, lda, B, ldb, ep, splits, st));
@@ -840,15 +840,16 @@ static mdnn_status_t gemm_dispatch32(mdnn_layout_t layout, int64_t M, int64_t N,
     splits = plan.splits;
   }
   // fp32 on the matrix cores (157 TFLOP/s; the vector-ALU kernel below stays
-  // under 79): NN 1024 x 2048 x 2048 198 -> 87 us, 4096^3 2045 -> 1008 us,
-  // 1000^3 89 -> 29 us.  Contiguous extents below 4 keep the kernel below.
+  // under 79): NN 1024 x 2048 x 2048 198 -> 75 us, 4096^3 2045 -> 1003 us,
+  // 1000^3 89 -> 25 us.  Contiguous extents below 4 keep the kernel below.
   // Nor products of few K steps and many outputs in 16-byte rows: those are
   // stores, and a K step below that is half as long and six workgroups of which
   // fit a CU wastes less before them (TN 7718 x 6080 x 8: 42 us, 60 on the
   // matrix cores, 1600 x 6016 x 16 13.1 and 19.5, NT 3115 x 1472 x 45 14.4 and
-  // 19.0; K of 64 level at 2^21 outputs; unaligned rows are quicker above).
+  // 19.0; level from K of 64 on; two 64 x 64 tiles per CU, TN 1024 x 2048 x 32,
+  // take 7.5 us there and 6.3 above, and unaligned rows are quicker above).
   const int64_t few_outputs = layout == MDNN_TN ? 1 << 20 : 1 << 17;
-  const bool shallow = splits == 1 && ep.vec4 && ((K <= 16 && M * N >= few_outputs) || (K <= 48 && M * N >= 1 << 21));
+  const bool shallow = splits == 1 && ep.vec4 && ((K <= 16 && M * N >= few_outputs) || (K <= 48 && ceil_div(M, 64) * ceil_div(N, 64) > 512));
   if (!shallow && gemm_reg_ok(MDNN_F32, layout, M, N, K, lda, ldb, splits)) {
     MDNN_TRY(gemm_reg(MDNN_F32, MDNN_F32, layout, M, N, K, A, lda, B, ldb, ep, splits, st));
     return split ? reduce_epilogue<F32, F32>(ws, splits, M, N, ep_in, st) : MDNN_SUCCESS;

@@ -20,10 +20,10 @@
 // is M or N are fetched from inside the row: they feed outputs that are
 // never stored.
 //
-// What bounds it: fp32 products the matrix cores (busy 86% of the time at
-// 4096^3, 136 TFLOP/s; 66% at 1024 x 2048 x 2048 where the launch and the
-// first loads show); 16-bit ones the LDS writes and their barrier (4001 x
-// 3999 x 4003: 610-650 TFLOP/s, about half of the direct-to-LDS kernel on
+// What bounds it: fp32 products the matrix cores (137 TFLOP/s at 4096^3; busy
+// 62-64% of the time at 1024 x 2048 x 2048, 114 TFLOP/s, where the launch and
+// the first loads show); 16-bit ones the LDS writes and their barrier (4001 x
+// 3999 x 4003: 676-694 TFLOP/s, about half of the direct-to-LDS kernel on
 // aligned operands).  Reading the second half step's fragments ahead of the
 // first half's MFMAs spilled registers and gained nothing.
 //
@@ -702,7 +702,7 @@ gemm_reg_kernel(typename LA::Args aa, typename LB::Args ba, int64_t M, int64_t N
   int t = 0;
   // Everything fetched so far has landed before the steady loop: with loads of
   // the branches above outstanding at its head the compiler waits there for
-  // every load in flight, once per round (fp32 NN 1024 x 2048 x 2048: 87 -> 77 us).
+  // every load in flight, once per round (fp32 NN 1024 x 2048 x 2048 takes a tenth longer).
   if (U + NR <= n1) __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
   for (; t + U + NR <= n1; t += U)
     steps<T, TL, NR, LA, LB, 0, U, false, NA>(t, n1, sa, sb, wa, wb, wm, wn, fa, fb, la, lb, s, accs);

@@ -20,25 +20,29 @@ void launch(const reg::MatArgs& a, const reg::MatArgs& b, int64_t M, int64_t N, 
 // workgroups, four register sets: their steps are shorter than a load).
 // Products of at most two 16-bit K steps are all first load and stores: as many
 // 64 x 64 workgroups per CU as registers allow (bf16 TN 2176 x 1024 x 38 8.3 ->
-// 6.5 us, 320 x 6784 x 70 9.4 -> 6.8).
-// fp32 ones of at most four steps take 64 x 64 tiles also where the 128 x 128
+// 6.5 us, 320 x 6784 x 70 9.4 -> 6.8; under larger outputs the 128 x 128 tiles
+// are up to a fifth quicker).
+// fp32 ones of two to four whole steps take 64 x 64 tiles also where the 128 x 128
 // ones would be just over one per CU (NT 663 x 5440 x 128 26.3 -> 17.2 us, NN 939
-// x 4160 x 88 22.5 -> 15.7; from 385 tiles on the large ones are level or ahead).
+// x 4160 x 88 22.5 -> 15.7; from 385 tiles on, and below K of 64, the large ones
+// are level or ahead).
 template <class T, class OutT, bool A_KC, bool B_KC>
 void run(const reg::MatArgs& a, const reg::MatArgs& b, int64_t M, int64_t N, int64_t K, const Epilogue& ep,
          int splits, hipStream_t st) {
+  constexpr bool H = reg::El<T>::ES == 2;
   const int64_t tiles = ceil_div(M, 128) * ceil_div(N, 128) * splits;
   const bool shallow = K <= 128 && splits == 1;
-  if constexpr (reg::El<T>::ES == 2) {
+  if (M > 64 && N > 64 && tiles >= (!H && shallow && K >= 64 ? 385 : 256)) {
+    launch<T, OutT, reg::TileR128, 2, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
+    return;
+  }
+  if constexpr (H) {
     if (shallow && M * N >= (1 << 18)) {
       launch<T, OutT, reg::TileR64Shallow, 2, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
       return;
     }
   }
-  if (M > 64 && N > 64 && tiles >= (shallow ? 385 : 256))
-    launch<T, OutT, reg::TileR128, 2, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
-  else
-    launch<T, OutT, reg::TileR64, 4, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
+  launch<T, OutT, reg::TileR64, 4, A_KC, B_KC>(a, b, M, N, K, ep, splits, st);
 }
 
 template <class T, class OutT>
