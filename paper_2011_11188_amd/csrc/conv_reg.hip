@@ -82,6 +82,11 @@ mdnn_status_t conv_reg_bwd_data(const ConvGeom& g, const void* dy, const void* w
   const Sizes z(g, io);
   const int64_t len = (int64_t)g.s * g.k, lp = round_up(len, z.E), K = g.r * lp, M = (int64_t)g.n * g.h * g.w;
   if (!z.ok() || !div_ok(K + 128, lp) || !div_ok(lp, g.k)) return MDNN_SUCCESS;
+  // fp32 layers of one chunk's reduction and many 16-byte outputs are stores: a
+  // K step of 32 before them costs more than the general kernel's of 16 (192 ->
+  // 2 channels, 1x1, 14 x 63 x 63: 31.6 us here, 25.0 there; with 5 to 16 within
+  // a tenth of each other)
+  if (io == MDNN_F32 && (int64_t)g.r * g.s * g.k <= 4 && g.c % 4 == 0 && M * g.c >= (1 << 22)) return MDNN_SUCCESS;
   const reg::RunArgs a{dy,  (int32_t)z.y, g.r,           (int32_t)len,    (int32_t)lp, magic_of(lp), g.ho, g.wo * g.k, g.k,
                        g.h, g.w,          g.r - 1 - g.pad, g.s - 1 - g.pad, 0,           M};
   const reg::RunArgs b{w, (int32_t)z.w, g.r, (int32_t)len, (int32_t)lp,      magic_of(lp), g.k, g.s,

@@ -33,6 +33,8 @@ SHAPES = [
     # 128 x 128 tiles in both directions (518 of them forward, also enough for
     # fp32); 128 x 64 forward with a reduction too long to be gathered
     (2, 182, 184, 70, 70, 1, 3, 0), (2, 182, 184, 70, 60, 1, 3, 0),
+    # 2^22 outputs backward, either side of the shortest reduction's rule
+    (2, 128, 129, 128, 4, 1, 1, 0), (2, 128, 129, 128, 5, 1, 1, 0),
 ]
 
 
