@@ -75,12 +75,13 @@ size_t im2col_bytes(const ConvGeom& g, mdnn_dtype_t io) {
 }
 
 // The automatic choice.  Forward timings on MI355X at the workloads' batch
-// sizes (microseconds; implicit GEMM / im2col + GEMM / Winograd):
-//   5x5,   1 ->  32 at 28x28, n 256 (bf16, bias+ReLU):  27.0 /  67.8 /   -
-//   5x5,  32 ->  64 at 14x14, n 256 (bf16, bias+ReLU):  17.4 /  50.5 /   -
-//   3x3,  64 ->  64 at 32x32, n 128 (fp16):             20.2 /  74.5 / 88.2
-//   3x3, 128 -> 128 at 16x16, n 128 (fp16):             15.6 /  47.4 / 57.4
-//   3x3, 256 -> 256 at  8x8,  n 128 (fp16):             22.1 /  36.0 / 37.5
+// sizes (microseconds; the plain forward pass, whichever kernel it takes / im2col +
+// GEMM / Winograd):
+//   5x5,   1 ->  32 at 28x28, n 256 (bf16, bias+ReLU):  11.0 /  44.9 /   -
+//   5x5,  32 ->  64 at 14x14, n 256 (bf16, bias+ReLU):  14.4 /  46.9 /   -
+//   3x3,  64 ->  64 at 32x32, n 128 (fp16):             17.3 /  67.9 / 85.2
+//   3x3, 128 -> 128 at 16x16, n 128 (fp16):             15.2 /  42.2 / 56.6
+//   3x3, 256 -> 256 at  8x8,  n 128 (fp16):             16.6 /  35.4 / 38.0
 // The stored im2col matrix is r*s times the input, written once and read
 // back by the GEMM: at these sizes that traffic costs more than the implicit
 // GEMM's per-tap gathers through L2, so every entry is the implicit GEMM.

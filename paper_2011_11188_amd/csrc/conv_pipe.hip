@@ -5,8 +5,8 @@
 //
 // Tiles:
 //   forward / backward data: 256 x 64 when N <= 64 (8 waves of 64 x 32; 128 x
-//   64 where those would leave CUs idle) or the last 128 columns would be half
-//   empty; else 128 x 128 (8 waves of 64 x 32), or 64 x 128 (4 waves of 32 x 64)
+//   64 where those would leave CUs idle) or, by the loaders for channel counts
+//   that are no multiple of 64, the last 128 columns would be half empty; else 128 x 128 (8 waves of 64 x 32), or 64 x 128 (4 waves of 32 x 64)
 //   when 128 x 128 tiles would leave CUs idle (3x3, 256 -> 256 at 8x8,
 //   batch 128: 128 tiles; forward 21.1 -> 16.3 us, backward data 23.0 ->
 //   18.8 us); 2 stages.
