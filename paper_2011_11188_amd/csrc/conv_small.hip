@@ -4,7 +4,9 @@
 // 64): the GEMM engine would spend almost all of a tile on padding.  Each
 // block accumulates every filter element over its chunk of output pixels
 // into fp32 partials, which the split reduction then sums in a fixed order
-// (deterministic).  (The forward passes: conv_gather.hip.)
+// (deterministic).  Taken for fewer than 8 output channels, and by 16-bit
+// images of less than one 16-byte chunk; the register-staged kernel takes the
+// rest.  (The forward passes: conv_gather.hip.)
 #include "conv_small.h"
 
 #include "conv_reg.h"

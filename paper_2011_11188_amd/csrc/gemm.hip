@@ -596,7 +596,8 @@ mdnn_status_t column_sums_final(const ColsumBatch& b, int32_t* nonfinite, hipStr
 // ---------------------------------------------------------------------------
 // A grid of few 64 x 64 tiles over K >= 64 is bound by the latency of its
 // serial K loop: split K so that about 256 workgroups run, each over at
-// least two K steps.
+// least 32 k (one step of the matrix-core kernel, two of the vector-ALU one; in
+// multiples of the latter's 16, so the former may end a split inside a step).
 static SplitPlan f32_split_plan(int64_t M, int64_t N, int64_t K) {
   SplitPlan p{1, K};
   const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
